@@ -76,7 +76,7 @@ def _log(rng, lo, hi):
     return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
 
 
-_MOST_EDGES = {"wiki": 3_000_000, "gdelt": 100_000_000, "mag": 200_000_000, "powerlaw": 60_000_000}
+_MOST_EDGES = {"wiki": 3_000_000, "gdelt": 100_000_000, "mag": 150_000_000, "powerlaw": 60_000_000}
 
 
 def _draw_graph(rng):
