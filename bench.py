@@ -100,7 +100,7 @@ def strip_comments(src):
     return "\n".join(l.rstrip() for l in "".join(out).splitlines() if l.strip())
 
 
-def kernel_source_hash(files=("tgl_internal.hpp", "tgl_cells.hpp", "tgl_sample.hip")):
+def kernel_source_hash(files=("tgl_internal.hpp", "tgl_cells.hpp", "tgl_search.hpp", "tgl_sample.hip")):
     """Hash of the code (comments left out) of the sources that define the
     measured kernels, to tell whether committed counters still apply."""
     h = hashlib.sha256()

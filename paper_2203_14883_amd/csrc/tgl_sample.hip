@@ -31,8 +31,7 @@
 // device and the next hop's kernels read them.
 #include <mutex>
 
-#include "tgl_cells.hpp"
-#include "tgl_internal.hpp"
+#include "tgl_search.hpp"
 
 namespace tgl {
 namespace {
@@ -69,11 +68,13 @@ struct HopArgs {
     const int32_t *p_nbr;
     const float *p_ts;
     const int32_t *p_local;     // previous hop's groups: exclusive offset within the scan tile ...
-    const int64_t *p_tile;      // ... plus the exclusive offset of the tile (kScanTile groups)
+    const int64_t *p_tile;      // ... plus the exclusive offset of the tile (kScanTile groups); null when
+                                // no scan was launched: p_local then holds the groups' raw counts
     const int32_t *p_s;         // window of each previous-hop group (null: hop 1 groups)
     const float *p_t0;          // hop-1 ancestor time of each previous-hop group (anchor A, hops >= 3)
     const uint64_t *p_path;     // path of each previous-hop group (null: hop 1 groups)
     int32_t p_k;                // fanout of the previous hop
+    uint64_t p_recip;           // floor(2^64 / p_k) + 1 (p_k > 1): see slot_group
     int64_t p_groups_static;    // previous hop's groups (hop 1 groups: R*S) ...
     const int64_t *p_groups_dyn; // ... or read on the device (roots of hop >= 2)
     const uint8_t *p_first;     // TGL_NBR_FIRST hint of each previous-hop slot, or null
@@ -84,6 +85,7 @@ struct HopArgs {
     int32_t hop;                // 1-based
     int32_t k;
     int32_t windows;            // windows per root: S on hop 1, 1 afterwards
+    int32_t chunk;              // candidate roots per wavefront and round: 64, or fewer for small calls
     float delta;
     int32_t delta_inf;
     int32_t anchor;             // TGL_ANCHOR_OWN / TGL_ANCHOR_ROOT (windows of hops >= 2)
@@ -102,368 +104,8 @@ struct HopArgs {
     uint8_t *o_first;           // TGL_NBR_FIRST hint of each slot, for the next hop (or null)
     uint2 *o_win;               // hist of each valid slot's entry, for the next hop (WIN kernels)
     int64_t *count0_out;        // hop 1 stores its root count here
+    int64_t *count_out;         // hops >= 2 without a scan before them store theirs here
 };
-
-// ts[p4 .. p4+3] for p4 a multiple of 4; entries at or past M read as +inf
-// (they are never inside a window).
-__device__ __forceinline__ float4 load_ts4(const float *__restrict__ tsa, uint32_t p4, uint32_t M) {
-    if (static_cast<uint64_t>(p4) + 3 < M) return *reinterpret_cast<const float4 *>(tsa + p4);
-    const float inf = __builtin_inff();
-    float4 r = make_float4(inf, inf, inf, inf);
-    if (p4 < M) r.x = tsa[p4];
-    if (static_cast<uint64_t>(p4) + 1 < M) r.y = tsa[p4 + 1];
-    if (static_cast<uint64_t>(p4) + 2 < M) r.z = tsa[p4 + 2];
-    return r;
-}
-
-// A stretch of a time-sorted run held in the registers of one G-lane group:
-// lane gl holds the H timestamps p0 .. p0 + H - 1, p0 = (lo & ~3) + H * gl,
-// loaded as H / 4 aligned float4.  One load covers any [lo, hi) of at most
-// `span` entries.
-template <int G>
-struct HeldRun {
-    static constexpr int NV = G >= 16 ? 1 : 16 / G;     // float4 per lane
-    static constexpr uint32_t H = 4 * NV;               // timestamps per lane
-    static constexpr uint32_t span = H * G - 3;
-    float4 v[NV];
-    uint32_t p0;
-};
-
-template <int G>
-__device__ __forceinline__ HeldRun<G> load_run(const float *__restrict__ tsa, uint32_t lo, uint32_t hi,
-                                               uint32_t M, int gl) {
-    HeldRun<G> r;
-    r.p0 = (lo & ~3u) + HeldRun<G>::H * static_cast<uint32_t>(gl);
-    const float inf = __builtin_inff();
-#pragma unroll
-    for (int m = 0; m < HeldRun<G>::NV; m++) {
-        const uint32_t p4 = r.p0 + 4 * m;
-        r.v[m] = p4 < hi && lo < hi ? load_ts4(tsa, p4, M) : make_float4(inf, inf, inf, inf);
-    }
-    return r;
-}
-
-// The run [a, b), b - a <= TGL_NODE_INLINE, held from the inline timestamps
-// of its node record rec (16-byte words 1..7): position a + i is inline
-// timestamp i, so the stretch starts at a and count_in applies unchanged.
-template <int G>
-__device__ __forceinline__ HeldRun<G> load_inline(const int4 *__restrict__ rec, uint32_t a, int gl) {
-    constexpr int kWords = TGL_NODE_INLINE / 4;
-    static_assert(HeldRun<G>::H * G >= TGL_NODE_INLINE, "held stretch covers the inline timestamps");
-    HeldRun<G> r;
-    r.p0 = a + HeldRun<G>::H * static_cast<uint32_t>(gl);
-    const float inf = __builtin_inff();
-#pragma unroll
-    for (int m = 0; m < HeldRun<G>::NV; m++) {
-        const int q = HeldRun<G>::NV * gl + m;
-        if (q < kWords) {
-            const int4 w = rec[1 + q];
-            r.v[m] = make_float4(__int_as_float(w.x), __int_as_float(w.y), __int_as_float(w.z), __int_as_float(w.w));
-        } else {
-            r.v[m] = make_float4(inf, inf, inf, inf);
-        }
-    }
-    return r;
-}
-
-// Sum over the G lanes of the calling lane's group.
-template <int G>
-__device__ __forceinline__ int group_sum(int c) {
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) c += __shfl_xor(c, off, kWave);
-    return c;
-}
-
-// lo + #{p in [lo, hi): ts[p] < v} for [lo, hi) inside the held stretch.
-template <int G>
-__device__ __forceinline__ uint32_t count_in(const HeldRun<G> &r, uint32_t lo, uint32_t hi, float v) {
-    int c = 0;
-#pragma unroll
-    for (int m = 0; m < HeldRun<G>::NV; m++) {
-        const uint32_t p = r.p0 + 4 * m;
-        c += (p >= lo && p < hi && r.v[m].x < v);
-        c += (p + 1 >= lo && p + 1 < hi && r.v[m].y < v);
-        c += (p + 2 >= lo && p + 2 < hi && r.v[m].z < v);
-        c += (p + 3 >= lo && p + 3 < hi && r.v[m].w < v);
-    }
-    return lo + static_cast<uint32_t>(group_sum<G>(c));
-}
-
-// For each i: lo[i] += #{p in [lo[i], hi[i]): arr[p] < v[i]}, over a sorted
-// stretch of arr (n_arr elements), found by the G lanes of one group together.
-// While a range is longer than one held stretch, each round probes G evenly
-// spaced positions of it; the probes below v[i] form a prefix, whose length
-// narrows the range to one gap; the last range is loaded whole and counted.
-// The NE searches advance together, so the probes of one round, and the final
-// loads, of all of them are in flight at the same time: the chain of dependent
-// loads is that of one search.
-template <int G, int NE>
-__device__ __forceinline__ void search_n(const float *__restrict__ arr, uint32_t n_arr, uint32_t (&lo)[NE],
-                                         uint32_t (&hi)[NE], const float (&v)[NE], int gl) {
-    for (;;) {
-        bool any = false;
-#pragma unroll
-        for (int i = 0; i < NE; i++) any |= hi[i] - lo[i] > HeldRun<G>::span;
-        if (!any) break;                            // group-uniform
-        // probes at lo + j * step, j = 1..G, step = len / (G + 1) >= 1: all
-        // inside (lo, hi), strictly increasing
-        float probe[NE];
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            probe[i] = 0.0f;
-            const uint32_t len = hi[i] - lo[i];
-            if (len > HeldRun<G>::span)
-                probe[i] = arr[lo[i] + static_cast<uint32_t>(gl + 1) * (len / (G + 1))];
-        }
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            const uint32_t len = hi[i] - lo[i];
-            if (len > HeldRun<G>::span) {           // group-uniform
-                const uint32_t step = len / (G + 1);
-                const uint32_t c = static_cast<uint32_t>(__popcll(group_ballot<G>(probe[i] < v[i])));
-                // probes 1..c are below v[i], probe c+1 (if any) is not
-                const uint32_t nlo = c > 0 ? lo[i] + c * step + 1 : lo[i];
-                if (c < G) hi[i] = lo[i] + (c + 1) * step;
-                lo[i] = nlo;
-            }
-        }
-    }
-    bool open = false;
-#pragma unroll
-    for (int i = 0; i < NE; i++) open |= hi[i] > lo[i];
-    if (!open) return;                              // group-uniform: every answer is known
-    HeldRun<G> r[NE];
-#pragma unroll
-    for (int i = 0; i < NE; i++) r[i] = load_run<G>(arr, lo[i], hi[i], n_arr, gl);
-#pragma unroll
-    for (int i = 0; i < NE; i++) lo[i] = count_in<G>(r[i], lo[i], hi[i], v[i]);
-}
-
-// A node's run [a, b) and its first and last timestamps: where a threshold
-// falls in it is estimated by linear interpolation between them.
-struct RunShape {
-    uint32_t a, b;
-    float first, last;
-};
-
-// Estimated position of threshold v in the run (lower bound: the count of
-// timestamps below v, plus a), and the spread of that estimate: if the
-// run's timestamps were independent draws between first and last, the count
-// below v would be binomial, with standard deviation at most sqrt(b - a) / 2.
-__device__ __forceinline__ void run_estimate(const RunShape &rs, float v, uint32_t &pos, uint32_t &spread) {
-    const float n = static_cast<float>(rs.b - rs.a);
-    float f = (v - rs.first) / (rs.last - rs.first);
-    if (!(f >= 0.0f)) f = f < 0.0f ? 0.0f : 0.5f;                 // below the run, or NaN
-    if (f > 1.0f) f = 1.0f;
-    const float o = f * n;                                         // <= n
-    pos = rs.a + (o < n ? static_cast<uint32_t>(o) : rs.b - rs.a);
-    spread = static_cast<uint32_t>(0.5f * __builtin_sqrtf(n)) + 1u;
-}
-
-// Probe g of a guided round: c + (g - G/2) d + d/2, clamped into [lo, hi).
-// Non-decreasing in g.
-template <int G>
-__device__ __forceinline__ uint32_t guided_pos(uint32_t lo, uint32_t hi, uint32_t c, uint32_t d, int g) {
-    const int64_t q = static_cast<int64_t>(c) + (static_cast<int64_t>(g) - G / 2) * static_cast<int64_t>(d) +
-                      static_cast<int64_t>(d / 2);
-    const int64_t last = static_cast<int64_t>(hi) - 1;
-    return static_cast<uint32_t>(q < static_cast<int64_t>(lo) ? static_cast<int64_t>(lo) : (q > last ? last : q));
-}
-
-// One round of the search of a sorted stretch of arr, guided by estimates:
-// for each i whose range [lo[i], hi[i]) is longer than a held stretch, the G
-// lanes probe positions d[i] apart around c[i].  The probes below v[i] form
-// a prefix (arr is sorted and the positions do not decrease), so the answer
-// lies after the last of them and at or before the next: the range shrinks
-// to about d[i] when the estimate is off by less than G/2 spacings, and
-// never grows.  lo[i] + #{p in [lo[i], hi[i]): arr[p] < v[i]} is unchanged.
-template <int G, int NE>
-__device__ __forceinline__ void guided_round(const float *__restrict__ arr, uint32_t (&lo)[NE], uint32_t (&hi)[NE],
-                                             const float (&v)[NE], const uint32_t (&c)[NE], const uint32_t (&d)[NE],
-                                             int gl) {
-    float probe[NE];
-#pragma unroll
-    for (int i = 0; i < NE; i++) {
-        probe[i] = 0.0f;
-        if (hi[i] - lo[i] > HeldRun<G>::span) probe[i] = arr[guided_pos<G>(lo[i], hi[i], c[i], d[i], gl)];
-    }
-#pragma unroll
-    for (int i = 0; i < NE; i++) {
-        if (hi[i] - lo[i] > HeldRun<G>::span) {     // group-uniform
-            const int n = __popcll(group_ballot<G>(probe[i] < v[i]));
-            const uint32_t nlo = n > 0 ? guided_pos<G>(lo[i], hi[i], c[i], d[i], n - 1) + 1 : lo[i];
-            if (n < G) hi[i] = guided_pos<G>(lo[i], hi[i], c[i], d[i], n);
-            lo[i] = nlo;
-        }
-    }
-}
-
-// Positions below NE thresholds, each in a range of its own: out[i] = lo0[i]
-// + #{p in [lo0[i], hi0[i]): ts[p] < v[i]} for each i with act[i] (lo0[i] otherwise),
-// each range a stretch of one sorted run.  Ranges longer than one probe round
-// are narrowed on the search index first when there is one.
-template <int G, int NE>
-__device__ __forceinline__ void count_below_ranges(const float *__restrict__ tsa, uint32_t M,
-                                                   const float *__restrict__ tsx, uint32_t nx,
-                                                   const uint32_t (&lo0)[NE], const uint32_t (&hi0)[NE],
-                                                   const float (&v)[NE], const bool (&act)[NE],
-                                                   uint32_t (&out)[NE], int gl) {
-    constexpr uint32_t X = TGL_INDEX_STRIDE;
-    uint32_t lo[NE], hi[NE];
-    bool any_index = false;
-#pragma unroll
-    for (int i = 0; i < NE; i++) {
-        const bool use = act[i] && tsx && hi0[i] - lo0[i] > HeldRun<G>::span * (G + 1);
-        const uint32_t ja = lo0[i] / X + (lo0[i] % X != 0);
-        const uint32_t jb = hi0[i] / X + (hi0[i] % X != 0);
-        lo[i] = use ? ja : lo0[i];
-        hi[i] = use ? jb : lo0[i];
-        any_index |= use;
-    }
-    if (any_index) {                                // group-uniform
-        search_n<G, NE>(tsx, nx, lo, hi, v, gl);
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            const bool use = act[i] && tsx && hi0[i] - lo0[i] > HeldRun<G>::span * (G + 1);
-            const uint32_t ja = lo0[i] / X + (lo0[i] % X != 0);
-            const uint32_t jb = hi0[i] / X + (hi0[i] % X != 0);
-            const uint32_t r = lo[i];
-            lo[i] = use ? (r > ja ? (r - 1) * X + 1 : lo0[i]) : lo0[i];   // ts[(r-1) X] < v[i]
-            hi[i] = use ? (r < jb ? r * X : hi0[i]) : (act[i] ? hi0[i] : lo0[i]);   // ts[r X] >= v[i]
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            lo[i] = lo0[i];
-            hi[i] = act[i] ? hi0[i] : lo0[i];
-        }
-    }
-    search_n<G, NE>(tsa, M, lo, hi, v, gl);
-#pragma unroll
-    for (int i = 0; i < NE; i++) out[i] = act[i] ? lo[i] : lo0[i];
-}
-
-// Positions below NE thresholds in [lo0, hi0), a range of the run [rs.a,
-// rs.b), from the run's time directory (tgl_cell per search-index slot; the
-// run owns K >= 1 cells), as count_below_n returns them: threshold i falls in cell
-// k = cell(v[i]), whose first position pos and timestamp, and the next
-// cell's pos (rs.b after the last cell), are read with one round of loads.
-// The run's count below v[i] is pos when v[i] <= ts[pos], else it lies in
-// [pos + 1, next pos], a stretch of about TGL_INDEX_STRIDE entries when the
-// run's timestamps are spread evenly, which count_below_ranges searches
-// (with the index when it is long).  Clamping the stretch into [lo0, hi0)
-// gives the count within that range.  Every position read from the
-// directory is clamped into the run.
-template <int G, int NE>
-__device__ __forceinline__ void count_below_dir(const float *__restrict__ tsa, uint32_t M,
-                                                const float *__restrict__ tsx, uint32_t nx,
-                                                const uint2 *__restrict__ dir, uint32_t lo0, uint32_t hi0,
-                                                const RunShape &rs, const float (&v)[NE], const bool (&act)[NE],
-                                                uint32_t (&out)[NE], int gl) {
-    constexpr uint32_t X = TGL_INDEX_STRIDE;
-    const uint32_t ja = rs.a / X + (rs.a % X != 0);
-    const uint32_t K = rs.b / X + (rs.b % X != 0) - ja;
-    const float sc = dir_scale(rs.first, rs.last, K);
-    uint2 c0[NE];
-    uint32_t c1[NE];
-#pragma unroll
-    for (int i = 0; i < NE; i++) {
-        c0[i] = make_uint2(rs.a, 0u);
-        c1[i] = rs.b;
-        if (act[i]) {                               // group-uniform
-            const uint32_t kc = dir_cell(v[i], rs.first, rs.last, sc, K);
-            c0[i] = dir[ja + kc];
-            if (kc + 1 < K) c1[i] = dir[ja + kc + 1].x;
-        }
-    }
-    uint32_t lo[NE], hi[NE];
-    bool open[NE];
-#pragma unroll
-    for (int i = 0; i < NE; i++) {
-        const uint32_t pos = c0[i].x < rs.a ? rs.a : (c0[i].x > rs.b ? rs.b : c0[i].x);
-        const uint32_t nxt = c1[i] < pos ? pos : (c1[i] > rs.b ? rs.b : c1[i]);
-        const bool past = v[i] > __uint_as_float(c0[i].y) && pos < nxt;
-        uint32_t l = past ? pos + 1 : pos;
-        uint32_t h = past ? nxt : l;
-        l = l < lo0 ? lo0 : (l > hi0 ? hi0 : l);
-        h = h < l ? l : (h > hi0 ? hi0 : h);
-        lo[i] = act[i] ? l : lo0;
-        hi[i] = act[i] ? h : lo0;
-        open[i] = act[i] && h > l;
-    }
-    count_below_ranges<G, NE>(tsa, M, tsx, nx, lo, hi, v, open, out, gl);
-}
-
-// Positions below NE thresholds in the time-sorted run [lo0, hi0) of the
-// timestamp array (M entries): out[i] = lo0 + #{p in [lo0, hi0): ts[p] < v[i]}
-// for each i with act[i] (out[i] = lo0 otherwise).  rec, when not null, is the
-// record of a node whose whole run (lo0 onwards) is inline in it: the run is
-// then read from there.  A run of at most one held stretch is loaded once and
-// serves every threshold.  A longer range starts from the time directory dir
-// of its run rs when there is one (count_below_dir).  Otherwise a range long
-// enough to need more than one probe round is first narrowed on the search
-// index tsx (nx samples, tsx[j] = ts[j * TGL_INDEX_STRIDE]) when there is
-// one, starting with a round guided by the run shape rs (the run that holds
-// the stretch, lo0 its start): with r the samples inside the run below v[i],
-// the answer lies after sample r - 1 and at or before sample r, fewer than
-// TGL_INDEX_STRIDE timestamps.
-template <int G, int NE, bool DIR>
-__device__ __forceinline__ void count_below_n(const float *__restrict__ tsa, uint32_t M,
-                                              const float *__restrict__ tsx, uint32_t nx,
-                                              const uint2 *__restrict__ dir,
-                                              const int4 *__restrict__ rec, uint32_t lo0, uint32_t hi0,
-                                              const RunShape &rs, const float (&v)[NE], const bool (&act)[NE],
-                                              uint32_t (&out)[NE], int gl) {
-    constexpr uint32_t X = TGL_INDEX_STRIDE;
-    if (rec || hi0 - lo0 <= HeldRun<G>::span) {    // group-uniform: one load serves every bound
-        const HeldRun<G> r = rec ? load_inline<G>(rec, lo0, gl) : load_run<G>(tsa, lo0, hi0, M, gl);
-#pragma unroll
-        for (int i = 0; i < NE; i++) out[i] = act[i] ? count_in<G>(r, lo0, hi0, v[i]) : lo0;
-        return;
-    }
-    if constexpr (DIR) {
-        // the range is longer than one held stretch, so its run owns a cell
-        count_below_dir<G, NE>(tsa, M, tsx, nx, dir, lo0, hi0, rs, v, act, out, gl);
-#pragma unroll
-        for (int i = 0; i < NE; i++)
-            if (!act[i]) out[i] = lo0;
-        return;
-    }
-    uint32_t lo[NE], hi[NE];
-    if (tsx && hi0 - lo0 > HeldRun<G>::span * (G + 1)) {   // group-uniform
-        // samples j in [ja, jb) are the positions j * X inside [lo0, hi0)
-        const uint32_t ja = lo0 / X + (lo0 % X != 0);
-        const uint32_t jb = hi0 / X + (hi0 % X != 0);
-        uint32_t gc[NE], gd[NE];
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            lo[i] = ja;
-            hi[i] = act[i] ? jb : ja;
-            uint32_t pos, spread;
-            run_estimate(rs, v[i], pos, spread);
-            gc[i] = pos / X;
-            gd[i] = spread / X > 0 ? spread / X : 1u;
-        }
-        guided_round<G, NE>(tsx, lo, hi, v, gc, gd, gl);
-        search_n<G, NE>(tsx, nx, lo, hi, v, gl);
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            const uint32_t r = lo[i];
-            lo[i] = r > ja ? (r - 1) * X + 1 : lo0;  // ts[(r-1) X] < v[i]
-            hi[i] = r < jb ? r * X : hi0;            // ts[r X] >= v[i]
-            if (!act[i]) hi[i] = lo[i];
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < NE; i++) {
-            lo[i] = lo0;
-            hi[i] = act[i] ? hi0 : lo0;
-        }
-    }
-    search_n<G, NE>(tsa, M, lo, hi, v, gl);
-#pragma unroll
-    for (int i = 0; i < NE; i++) out[i] = act[i] ? lo[i] : lo0;
-}
 
 // Window edges of a long run [a, b) found from saved positions -- the
 // per-node pointers of Section 3.1, kept for hop 1 -- by the G lanes of one
@@ -641,6 +283,13 @@ __device__ __forceinline__ void emit_at(const OutRow &o, uint32_t e, bool valid,
     }
 }
 
+// The previous hop's group of its slot v, v / p_k, without dividing: with
+// p_recip = (2^64 + e) / p_k, 0 < e <= p_k <= 1024, the product's high half is
+// the quotient for every v below 2^54, more slots than memory holds.
+__device__ __forceinline__ int64_t slot_group(const HopArgs &p, int64_t v) {
+    return p.p_k == 1 ? v : static_cast<int64_t>(__umul64hi(static_cast<uint64_t>(v), p.p_recip));
+}
+
 // A 64-bit value that is the same in every active lane, moved to scalar
 // registers.
 __device__ __forceinline__ int64_t uniform64(int64_t v) {
@@ -663,6 +312,48 @@ __device__ __forceinline__ void gather_records(const int4 *__restrict__ ent, uin
     }
 #pragma unroll
     for (int u = 0; u < U; u++) rec[u] = ent[pick[u] != UINT32_MAX ? pick[u] : 0u];
+}
+
+// Four counts loaded or stored at once; the caller's workspace, and so the
+// counts in it, may be aligned to 4 bytes only.
+using i32x4 = int __attribute__((ext_vector_type(4), aligned(4)));
+
+// Most groups whose counts are left unscanned: every wavefront of the next
+// hop then sums the counts before its chunk itself, 16 bytes per lane and
+// load (slots_before).  The two scan kernels take 9 us with their launches
+// whatever the size of a small call; summing instead costs the next hop
+// nothing at 1,800 groups (10.0 -> 9.5 us, 18,000 candidates) and 1.6 us at
+// 6,000 (10.0 -> 11.6 us, 60,000 candidates), growing with the groups.
+constexpr int64_t kUnscannedGroups = 8192;
+
+// Valid slots before slot v0, a wavefront-uniform value, from the groups' raw
+// counts (k slots per group, the valid ones a prefix): the counts of the
+// groups before v0's, plus v0's group's own slots before v0.  v0 lies in one
+// of the groups; cnt is padded to whole 16-byte words.
+__device__ __forceinline__ int64_t slots_before(const int32_t *__restrict__ cnt, int64_t v0, int64_t k) {
+    const uint32_t g0 = static_cast<uint32_t>(v0) / static_cast<uint32_t>(k);   // below kUnscannedGroups
+    const uint32_t j0 = static_cast<uint32_t>(v0) - g0 * static_cast<uint32_t>(k);
+    const int32_t own = cnt[g0];
+    int32_t sum = 0;                            // below kUnscannedGroups * TGL_MAX_FANOUT
+    constexpr uint32_t kStep = 4 * kWave;
+    for (uint32_t b = 4 * lane_id(); b < g0; b += 4 * kStep) {
+        i32x4 x[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t at = b + i * kStep;
+            x[i] = *reinterpret_cast<const i32x4 *>(cnt + (at < g0 ? at : 0u));   // clamped: loads issue together
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t at = b + i * kStep;
+            sum += (at < g0 ? x[i].x : 0) + (at + 1 < g0 ? x[i].y : 0) + (at + 2 < g0 ? x[i].z : 0) +
+                   (at + 3 < g0 ? x[i].w : 0);
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) sum += __shfl_xor(sum, d, kWave);
+    return static_cast<int64_t>(__builtin_amdgcn_readfirstlane(sum)) +
+           (static_cast<int64_t>(own) < static_cast<int64_t>(j0) ? own : static_cast<int32_t>(j0));
 }
 
 __device__ __forceinline__ void wave_sync_lds() {
@@ -785,13 +476,14 @@ __global__ __launch_bounds__(kBlock) void hop_multi_wide_kernel(const HopArgs p)
 
     const int64_t nv = p.num_roots;
     if (p.count0_out && blockIdx.x == 0 && threadIdx.x == 0) *p.count0_out = nv;
-    const int64_t nchunks = (nv + kWave - 1) / kWave;
+    const int chunk = p.chunk;
+    const int64_t nchunks = (nv + chunk - 1) / chunk;
 
     for (int64_t c = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + w; c < nchunks;
          c += static_cast<int64_t>(gridDim.x) * kWavesPerBlock) {
         // ---- phase 1: one lane per root ----
-        const int64_t v = c * kWave + lane;
-        const bool valid = v < nv;
+        const int64_t v = c * chunk + lane;
+        const bool valid = lane < chunk && v < nv;
         int32_t x = -1;
         float t = 0.0f;
         if (valid) {
@@ -810,12 +502,12 @@ __global__ __launch_bounds__(kBlock) void hop_multi_wide_kernel(const HopArgs p)
         }
         wave_sync_lds();
         // ---- phase 2: G lanes per root ----
-        const int64_t rem = nv - c * kWave;
-        const int nvalid = rem < kWave ? static_cast<int>(rem) : kWave;
+        const int64_t rem = nv - c * chunk;
+        const int nvalid = rem < chunk ? static_cast<int>(rem) : chunk;
         for (int base = 0; base < nvalid; base += GPW) {
             const int i = base + gw;
             if (i < nvalid) {                       // group-uniform
-                multi_root<G, MODE, LAST, PTR, DIR>(p, c * kWave + i, r_x[w][i], r_a[w][i], r_b[w][i], r_f[w][i], r_l[w][i],
+                multi_root<G, MODE, LAST, PTR, DIR>(p, c * chunk + i, r_x[w][i], r_a[w][i], r_b[w][i], r_f[w][i], r_l[w][i],
                                           r_t[w][i], r_hp[w][i], gl, my_edges);
             }
         }
@@ -867,7 +559,8 @@ __global__ __launch_bounds__(kBlock) void hop_multi_kernel(const HopArgs p) {
     const int nslots = W * k;                 // slots per root
     const int64_t nv = p.num_roots;
     if (p.count0_out && blockIdx.x == 0 && threadIdx.x == 0) *p.count0_out = nv;
-    const int64_t nchunks = (nv + kWave - 1) / kWave;
+    const int chunk = p.chunk;
+    const int64_t nchunks = (nv + chunk - 1) / chunk;
     const uint64_t hop_key = static_cast<uint64_t>(p.hop) << 40;
     // phase 3 serves slot e = lane + 64 n of a chunk in round n: its root
     // i = e / (W k), window s and rank j (e % (W k) = s k + j) start at those
@@ -882,8 +575,8 @@ __global__ __launch_bounds__(kBlock) void hop_multi_kernel(const HopArgs p) {
     for (int64_t c = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + w; c < nchunks;
          c += static_cast<int64_t>(gridDim.x) * kWavesPerBlock) {
         // ---- phase 1: one lane per root ----
-        const int64_t v = c * kWave + lane;
-        const bool valid = v < nv;
+        const int64_t v = c * chunk + lane;
+        const bool valid = lane < chunk && v < nv;
         int32_t x = -1;
         float t = 0.0f;
         if (valid) {
@@ -902,8 +595,8 @@ __global__ __launch_bounds__(kBlock) void hop_multi_kernel(const HopArgs p) {
             if constexpr (TAIL) r_vw[w][lane] = bound_value(t, W, p.delta);
         }
         wave_sync_lds();
-        const int64_t rem = nv - c * kWave;
-        const int nvalid = rem < kWave ? static_cast<int>(rem) : kWave;
+        const int64_t rem = nv - c * chunk;
+        const int nvalid = rem < chunk ? static_cast<int>(rem) : chunk;
 
         // ---- phase 2: G lanes per root locate its W + 1 window edges (W with TAIL) ----
         for (int base = 0; base < nvalid; base += GPW) {
@@ -959,7 +652,7 @@ __global__ __launch_bounds__(kBlock) void hop_multi_kernel(const HopArgs p) {
                 const uint32_t whi = r_e[w][i * kMultiEdges + s];
                 const uint32_t wlo = r_e[w][i * kMultiEdges + s + 1];
                 const uint32_t n = wlo < whi ? whi - wlo : 0u;
-                p.o_cnt[(c * kWave + i) * W + s] = MODE == TGL_MOST_RECENT
+                p.o_cnt[(c * chunk + i) * W + s] = MODE == TGL_MOST_RECENT
                                                        ? static_cast<int32_t>(n < static_cast<uint32_t>(k) ? n : k)
                                                        : (n > 0 ? k : 0);
             }
@@ -967,7 +660,7 @@ __global__ __launch_bounds__(kBlock) void hop_multi_kernel(const HopArgs p) {
 
         // ---- phase 3: one lane per slot ----
         const int total = nvalid * nslots;
-        const int64_t obase = c * kWave * static_cast<int64_t>(nslots);
+        const int64_t obase = c * chunk * static_cast<int64_t>(nslots);
         OutRow orow{p.o_nbr + obase, p.o_eid + obase, p.o_ts + obase, p.o_dt + obase, nullptr};
         if constexpr (!LAST) orow.first = p.o_first ? p.o_first + obase : nullptr;
         int ci = li0, cs = ls0, cj = lj0;           // (i, s, j) of this lane's slot in the round
@@ -1076,8 +769,8 @@ __device__ __forceinline__ void locate_window(const HopArgs &p, int32_t x, uint3
 // is not the last gathers the histories of its picks for the next hop.
 // DIR (a T-CSR with time directories): phase 2 starts the search of a long
 // run from its directory.
-template <int G, int MODE, bool LAST, bool FIRST, int NB, bool PTR, bool WIN, bool DIR>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !FIRST ? 4 : (NB == 1 ? 7 : 6)))) void hop_single_kernel(const HopArgs p) {
+template <int G, int MODE, bool LAST, bool FIRST, int NB, bool PTR, bool WIN, bool DIR, bool RAW = false>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu((WIN && !FIRST) || RAW ? 4 : (NB == 1 ? 7 : 6)))) void hop_single_kernel(const HopArgs p) {
     static_assert(FIRST || !PTR, "saved window edges are kept for hop 1 only");
     static_assert(!(PTR && DIR), "saved window edges replace the directory");
     static_assert(!WIN || NB == 1, "histories give windows unbounded below");
@@ -1088,7 +781,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
     // all its gathers at once (4 waves per SIMD instead of 8)
     constexpr int U = WIN && !FIRST ? 10 : 4;
     const int lane = lane_id();
-    const int w = threadIdx.x / kWave;
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
     const int gl = lane & (G - 1);
     const int gw = lane / G;
     __shared__ uint32_t r_lo[kWavesPerBlock][kWave];   // run start, then window start
@@ -1113,8 +806,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
     } else {
         const int64_t groups = p.p_groups_dyn ? *p.p_groups_dyn : p.p_groups_static;
         nv = groups * pk;
+        if (RAW && nv == 0 && blockIdx.x == 0 && threadIdx.x == 0) *p.count_out = 0;
     }
-    const int64_t nchunks = (nv + kWave - 1) / kWave;
+    const int chunk = p.chunk;
+    const int64_t nchunks = (nv + chunk - 1) / chunk;
     const uint64_t S = static_cast<uint64_t>(p.S);
     const uint64_t path1 = p.root_base * S * static_cast<uint64_t>(pk);   // hop-1 children: + v
     const int k = p.k;
@@ -1130,7 +825,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
     for (int64_t c = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + w; c < nchunks;
          c += static_cast<int64_t>(gridDim.x) * kWavesPerBlock) {
         // ---- phase 1: one lane per candidate root ----
-        const int64_t v = c * kWave + lane;
+        const int64_t v = c * chunk + lane;
+        const bool in = lane < chunk && v < nv;
         bool valid;
         int32_t x = -1;
         float t = 0.0f;
@@ -1138,8 +834,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
         int32_t s = 0;
         uint64_t path = 0;
         float ta = 0.0f;                        // the time the windows are placed at
+        uint64_t mask;                          // lanes with a root
+        int64_t q0 = 0;                         // index of the first of them (first hop, RAW)
         if constexpr (FIRST) {
-            valid = v < nv;
+            valid = in;
+            mask = __ballot(valid);
+            q0 = c * chunk;
             if (valid) {
                 x = p.rx[v];
                 t = p.rt[v];
@@ -1148,26 +848,37 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
                 path = p.root_base + static_cast<uint64_t>(v);
             }
         } else {
-            x = v < nv ? p.p_nbr[v] : -1;
+            // RAW: valid slots before the chunk, in flight with the slots
+            if constexpr (RAW) q0 = slots_before(p.p_local, c * chunk, pk);
+            x = in ? p.p_nbr[v] : -1;
             valid = x >= 0;
+            mask = __ballot(valid);
+            // the last chunk knows this hop's number of roots
+            if constexpr (RAW)
+                if (c == nchunks - 1 && lane == 0) *p.count_out = q0 + __popcll(mask);
             if (valid) {
                 t = p.p_ts[v];
                 ta = t;
-                const int64_t g = v / pk;
-                const int64_t j = v - g * pk;
-                q = p.p_tile[g / kScanTile] + p.p_local[g] + j;
-                if (p.p_s) {
-                    s = p.p_s[g];
-                    path = p.p_path[g] * static_cast<uint64_t>(pk) + static_cast<uint64_t>(j);
-                } else {
-                    s = static_cast<int32_t>(static_cast<uint64_t>(g) % S);
-                    path = path1 + static_cast<uint64_t>(v);
+                path = path1 + static_cast<uint64_t>(v);
+                // the previous hop's group of the slot: not needed for a RAW
+                // hop with one window at its own anchor, whose paths follow
+                // from the slots
+                if (!RAW || p.p_s || p.S > 1 || p.anchor == TGL_ANCHOR_ROOT) {
+                    const int64_t g = slot_group(p, v);
+                    if constexpr (!RAW) q = p.p_tile[g / kScanTile] + p.p_local[g] + (v - g * pk);
+                    if (p.p_s) {
+                        s = p.p_s[g];
+                        path = p.p_path[g] * static_cast<uint64_t>(pk) + static_cast<uint64_t>(v - g * pk);
+                    } else {
+                        s = static_cast<int32_t>(static_cast<uint64_t>(g) % S);
+                    }
+                    if (p.anchor == TGL_ANCHOR_ROOT) {
+                        // hop-1 ancestor: hop-2 roots come from hop-1 group (r, s) = g
+                        ta = p.p_t0 ? p.p_t0[g] : p.rt[static_cast<uint64_t>(g) / S];
+                    }
                 }
-                if (p.anchor == TGL_ANCHOR_ROOT) {
-                    // hop-1 ancestor: hop-2 roots come from hop-1 group (r, s) = g
-                    ta = p.p_t0 ? p.p_t0[g] : p.rt[static_cast<uint64_t>(g) / S];
-                    if (p.o_t0) p.o_t0[q] = ta;
-                }
+                if constexpr (RAW) q = q0 + rank_below(mask);
+                if (p.o_t0) p.o_t0[q] = ta;
                 p.o_parent[q] = v;
                 if (p.o_s) {
                     p.o_s[q] = s;
@@ -1207,13 +918,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
                 if (lo > hi) lo = hi;
             }
         }
-        const uint64_t mask = __ballot(valid);
         const uint64_t need_mask = __ballot(valid && need);
         if (valid) {
             const int r = rank_below(mask);
             r_lo[w][r] = need ? run.a : lo;
             r_n[w][r] = need ? run.b : hi - lo;
-            if (r == 0) r_q0[w] = q;             // packed roots are q0, q0 + 1, ...
+            if (!FIRST && !RAW && r == 0) r_q0[w] = q;   // packed roots are q0, q0 + 1, ...
             r_hp[w][r] = MODE == TGL_UNIFORM
                              ? mix64(p.seedmix ^ path) ^ hop_key ^ (static_cast<uint64_t>(static_cast<uint32_t>(s)) << 24)
                              : 0;
@@ -1248,7 +958,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
                     r_n[w][i] = whi - wlo;
                     if (p.o_cnt) {
                         const uint32_t n = whi - wlo;
-                        p.o_cnt[r_q0[w] + i] = MODE == TGL_MOST_RECENT
+                        p.o_cnt[(FIRST || RAW ? q0 : r_q0[w]) + i] = MODE == TGL_MOST_RECENT
                                                  ? static_cast<int32_t>(n < static_cast<uint32_t>(k) ? n : k)
                                                  : (n > 0 ? k : 0);
                     }
@@ -1261,7 +971,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
         // slot e of the chunk (root i = e / k, rank j = e % k) is output
         // q0 * k + e, packed roots having consecutive indices
         const int total = nvalid * k;
-        const int64_t obase = total > 0 ? uniform64(r_q0[w]) * k : 0;
+        const int64_t obase = total > 0 ? uniform64(FIRST || RAW ? q0 : r_q0[w]) * k : 0;
         OutRow orow{p.o_nbr + obase, p.o_eid + obase, p.o_ts + obase, p.o_dt + obase, nullptr, nullptr};
         if constexpr (!LAST && !WIN) orow.first = p.o_first ? p.o_first + obase : nullptr;
         if constexpr (!LAST && WIN) orow.win = p.o_win + obase;
@@ -1321,10 +1031,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WIN && !
     }
 }
 
+// A hop >= 2, after a scan of the previous hop's counts or (RAW) without.
+template <int MODE, bool LAST, int NB, bool WIN, bool DIR>
+void launch_later(const HopArgs &a, unsigned nb, hipStream_t st) {
+    if (a.p_tile) hop_single_kernel<8, MODE, LAST, false, NB, false, WIN, DIR, false><<<nb, kBlock, 0, st>>>(a);
+    else hop_single_kernel<8, MODE, LAST, false, NB, false, WIN, DIR, true><<<nb, kBlock, 0, st>>>(a);
+}
+
 template <int MODE, bool LAST>
 void launch_mode_last(int G, bool first, bool multi, bool win, const HopArgs &a, int64_t work, hipStream_t st) {
-    // `work` candidate roots (hop 1: roots; later hops: previous slots), 64 per wavefront
-    int64_t blocks = (work + kBlock - 1) / kBlock;
+    // `work` candidate roots (hop 1: roots; later hops: previous slots), a.chunk per wavefront
+    const int64_t per_block = static_cast<int64_t>(a.chunk) * kWavesPerBlock;
+    int64_t blocks = (work + per_block - 1) / per_block;
     if (blocks < 1) blocks = 1;
     if (blocks > kMaxGrid) blocks = kMaxGrid;
     const unsigned nb = static_cast<unsigned>(blocks);
@@ -1361,19 +1079,19 @@ void launch_mode_last(int G, bool first, bool multi, bool win, const HopArgs &a,
             if (ptr) hop_single_kernel<8, MODE, LAST, true, 1, true, true, false><<<nb, kBlock, 0, st>>>(a);
             else if (first && dir) hop_single_kernel<8, MODE, LAST, true, 1, false, true, true><<<nb, kBlock, 0, st>>>(a);
             else if (first) hop_single_kernel<8, MODE, LAST, true, 1, false, true, false><<<nb, kBlock, 0, st>>>(a);
-            else hop_single_kernel<8, MODE, LAST, false, 1, false, true, false><<<nb, kBlock, 0, st>>>(a);
+            else launch_later<MODE, LAST, 1, true, false>(a, nb, st);
         } else if (a.delta_inf) {
             if (ptr) hop_single_kernel<8, MODE, LAST, true, 1, true, false, false><<<nb, kBlock, 0, st>>>(a);
             else if (first && dir) hop_single_kernel<8, MODE, LAST, true, 1, false, false, true><<<nb, kBlock, 0, st>>>(a);
             else if (first) hop_single_kernel<8, MODE, LAST, true, 1, false, false, false><<<nb, kBlock, 0, st>>>(a);
-            else if (dir) hop_single_kernel<8, MODE, LAST, false, 1, false, false, true><<<nb, kBlock, 0, st>>>(a);
-            else hop_single_kernel<8, MODE, LAST, false, 1, false, false, false><<<nb, kBlock, 0, st>>>(a);
+            else if (dir) launch_later<MODE, LAST, 1, false, true>(a, nb, st);
+            else launch_later<MODE, LAST, 1, false, false>(a, nb, st);
         } else {
             if (ptr) hop_single_kernel<8, MODE, LAST, true, 2, true, false, false><<<nb, kBlock, 0, st>>>(a);
             else if (first && dir) hop_single_kernel<8, MODE, LAST, true, 2, false, false, true><<<nb, kBlock, 0, st>>>(a);
             else if (first) hop_single_kernel<8, MODE, LAST, true, 2, false, false, false><<<nb, kBlock, 0, st>>>(a);
-            else if (dir) hop_single_kernel<8, MODE, LAST, false, 2, false, false, true><<<nb, kBlock, 0, st>>>(a);
-            else hop_single_kernel<8, MODE, LAST, false, 2, false, false, false><<<nb, kBlock, 0, st>>>(a);
+            else if (dir) launch_later<MODE, LAST, 2, false, true>(a, nb, st);
+            else launch_later<MODE, LAST, 2, false, false>(a, nb, st);
         }
     }
 }
@@ -1395,6 +1113,31 @@ int pick_group(int64_t slots_per_root) {
     int g = 16;
     while (g < 64 && g < slots_per_root) g <<= 1;
     return g;
+}
+
+// Candidate roots per wavefront and round of a hop kernel with `work`
+// candidates.  A wavefront locates the windows of its chunk 64 / G = 8 roots
+// at a time, one round of dependent loads after the other, so a call that
+// leaves the chip's 1024 SIMDs mostly empty is as slow as one chunk: its
+// chunks are cut until there are wavefronts enough to hide those rounds.
+// Kernel times measured (us, chunks of 64 / 32 / 16 / 8 roots):
+//   hop 1, 1,800 roots, one window 25.0 / 15.7 / 10.7 / 8.7, three windows
+//   50.7 / 28.3 / 17.9 / 11.2; 18,000 roots 32.2 / 20.0 / 14.2 / 11.8; 60,000
+//   roots 30.8 / 20.8 / 16.9 / 17.3; 180,000 roots 45.0 / 36.4 / 38.0 / 43.3;
+//   768,000 roots in three windows 247 / 236 / 240 / 263.  So 32 at most, and
+//   halved while fewer than 3072 wavefronts would run;
+//   later hops that search, 54,000 candidates 32.8 / 21.2 / 16.6 / 17.4;
+//   180,000 35.2 / 29.9 / 30.7 / 35.9; 540,000 65.0 / 64.3 / 70.7 / 89.9;
+//   later hops with histories, which search nothing and gain only parallel
+//   gathers, 18,000 candidates 10.1 / 9.0 / 9.0 / 9.1; 60,000 12.1 / 11.3 /
+//   11.4 / 14.8; 1.8 million 86 / 96 / 138 / 223 (chunks of fewer roots write
+//   shorter stretches of every output array).
+int32_t pick_chunk(bool first, bool win, int64_t work) {
+    int32_t chunk = first ? 32 : 64;
+    const int32_t least = first ? 8 : 16;
+    const int64_t waves = first || !win ? 3072 : 1024;
+    while (chunk > least && work < waves * chunk) chunk /= 2;
+    return chunk;
 }
 
 // Saved window edges at the start of every run: pointers[i * N + x] = indptr[x]
@@ -1434,6 +1177,41 @@ bool sample_args_ok(int64_t R, int32_t hops, const int32_t *fanouts, int32_t S) 
     return true;
 }
 
+// The kScanItems counts from base on, a multiple of kScanItems: two 16-byte
+// loads, or one by one where they pass n.
+static_assert(kScanItems == 8, "two 16-byte words of counts per thread");
+__device__ __forceinline__ void load_counts(const int32_t *__restrict__ cnt, int64_t base, int64_t n,
+                                            int32_t (&v)[kScanItems]) {
+    if (base + kScanItems <= n) {
+        const i32x4 a = *reinterpret_cast<const i32x4 *>(cnt + base);
+        const i32x4 b = *reinterpret_cast<const i32x4 *>(cnt + base + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < kScanItems; i++) v[i] = base + i < n ? cnt[base + i] : 0;
+    }
+}
+
+// Writes the exclusive offsets of the counts v from `run` on in their place.
+__device__ __forceinline__ void store_offsets(int32_t *__restrict__ cnt, int64_t base, int64_t n, int32_t run,
+                                              const int32_t (&v)[kScanItems]) {
+    int32_t o[kScanItems];
+#pragma unroll
+    for (int i = 0; i < kScanItems; i++) {
+        o[i] = run;
+        run += v[i];
+    }
+    if (base + kScanItems <= n) {
+        *reinterpret_cast<i32x4 *>(cnt + base) = i32x4{o[0], o[1], o[2], o[3]};
+        *reinterpret_cast<i32x4 *>(cnt + base + 4) = i32x4{o[4], o[5], o[6], o[7]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < kScanItems; i++)
+            if (base + i < n) cnt[base + i] = o[i];
+    }
+}
+
 // Exclusive scan of a hop's per-group valid counts, first pass, tiles of
 // kScanTile groups per block: the counts are overwritten with each group's
 // offset within its tile, and the tile totals go to tile_off (which
@@ -1450,20 +1228,12 @@ __global__ __launch_bounds__(kBlock) void group_scan_kernel(int32_t *__restrict_
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile + static_cast<int64_t>(threadIdx.x) * kScanItems;
     int32_t v[kScanItems];
     int64_t sum = 0;
+    load_counts(cnt, base, n, v);
 #pragma unroll
-    for (int i = 0; i < kScanItems; i++) {
-        const int64_t idx = base + i;
-        v[i] = idx < n ? cnt[idx] : 0;
-        sum += v[i];
-    }
+    for (int i = 0; i < kScanItems; i++) sum += v[i];
     int64_t total;
     int64_t run = block_exclusive_sum<int64_t>(sum, lds, &total);
-#pragma unroll
-    for (int i = 0; i < kScanItems; i++) {
-        const int64_t idx = base + i;
-        if (idx < n) cnt[idx] = static_cast<int32_t>(run);        // < kScanTile * TGL_MAX_FANOUT
-        run += v[i];
-    }
+    store_offsets(cnt, base, n, static_cast<int32_t>(run), v);    // < kScanTile * TGL_MAX_FANOUT
     if (threadIdx.x == 0) tile_off[blockIdx.x] = total;
 }
 
@@ -1653,6 +1423,7 @@ tgl_status tgl_sample_ex(const tgl_tcsr *g, const int32_t *roots, const float *r
     a.seedmix = mix64(seed ^ kGolden);
 
     const int32_t S = num_snapshots;
+    bool scanned = false;                       // the previous hop's counts were scanned
     for (int h = 1; h <= hops; h++) {
         const bool last = h == hops;
         const int32_t k = fanouts[h - 1];
@@ -1683,8 +1454,10 @@ tgl_status tgl_sample_ex(const tgl_tcsr *g, const int32_t *roots, const float *r
             a.p_nbr = po.nbr;
             a.p_ts = po.ts;
             a.p_local = ws.cnt[(h - 1) & 1];
-            a.p_tile = ws.tile_off;
+            a.p_tile = scanned ? ws.tile_off : nullptr;
+            a.count_out = scanned ? nullptr : counts + (h - 1);
             a.p_k = fanouts[h - 2];
+            a.p_recip = a.p_k > 1 ? ~0ull / static_cast<uint64_t>(a.p_k) + 1 : 0;
             a.p_s = h >= 3 ? ws.s[(h - 1) & 1] : nullptr;
             a.p_path = h >= 3 ? ws.path[(h - 1) & 1] : nullptr;
             a.p_t0 = h >= 3 && anchor == TGL_ANCHOR_ROOT ? ws.t0[(h - 1) & 1] : nullptr;
@@ -1694,6 +1467,7 @@ tgl_status tgl_sample_ex(const tgl_tcsr *g, const int32_t *roots, const float *r
         const bool multi = h == 1 && S > 1;
         const int G = pick_group(static_cast<int64_t>(a.windows) * k);
         const int64_t work = h == 1 ? num_roots : cap[h - 1];
+        a.chunk = pick_chunk(h == 1, win, work);
         {
             ScopedTimer tm(h == 1 ? TGL_TIMER_HOP1 : TGL_TIMER_HOPN, st);
             launch_hop(G, mode, h == 1, multi, last, win, a, work, st);
@@ -1703,6 +1477,8 @@ tgl_status tgl_sample_ex(const tgl_tcsr *g, const int32_t *roots, const float *r
 
         // ---- exclusive scan of this hop's group counts -> next hop's indices ----
         const int64_t groups_cap = h == 1 ? num_roots * S : cap[h - 1];
+        scanned = groups_cap > kUnscannedGroups;
+        if (!scanned) continue;
         const int64_t *groups_dyn = h == 1 ? nullptr : counts + (h - 1);
         const int64_t tiles = scan_tiles(groups_cap) > 0 ? scan_tiles(groups_cap) : 1;
         ScopedTimer tm(TGL_TIMER_COMPACT, st);
