@@ -20,8 +20,9 @@
 //
 // The paper builds the T-CSR once on the host; here the same structure is
 // produced on the device from a COO that may be in any order.
-#include "tgl_cells.hpp"
-#include "tgl_internal.hpp"
+#include <type_traits>
+
+#include "tgl_search.hpp"
 
 namespace tgl {
 namespace {
@@ -581,81 +582,178 @@ __global__ __launch_bounds__(kBlock) void first_hint_kernel(int4 *__restrict__ e
     }
 }
 
+// f(integral_constant<int, I>) for I = 0 .. N - 1.
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, F, I + 1>(static_cast<F &&>(f));
+    }
+}
+
+// The value of lane I of the calling lane's 8-lane group, by two DPP moves:
+// within the quads, then from the quad that holds lane I to the other one.
+template <int I>
+__device__ __forceinline__ int bcast8(int v) {
+    const int a = __builtin_amdgcn_update_dpp(v, v, (I & 3) * 0x55, 0xf, 0xf, false);   // quad_perm: lane I % 4
+    if constexpr (I < 4) return __builtin_amdgcn_update_dpp(a, a, 0x114, 0xf, 0xa, false);   // row_shr:4 into odd quads
+    else return __builtin_amdgcn_update_dpp(a, a, 0x104, 0xf, 0x5, false);                  // row_shl:4 into even quads
+}
+
+// Sum over the 8 lanes of a group, in every lane.
+__device__ __forceinline__ int sum8(int v) {
+    v += __builtin_amdgcn_update_dpp(v, v, 0xb1, 0xf, 0xf, false);    // quad_perm [1, 0, 3, 2]
+    v += __builtin_amdgcn_update_dpp(v, v, 0x4e, 0xf, 0xf, false);    // quad_perm [2, 3, 0, 1]
+    return v + __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false);   // row_half_mirror: the other quad
+}
+
 // Neighbour histories (tgl_span): entry p with neighbour v and time t gets
 // hist[p] = {lo, hi}, lo the start of v's run and hi = lo + #{entries of v
 // with ts < t} -- where a root (v, t) of a later hop finds its candidates
 // when windows are unbounded below.  v's node record answers alone when t is
 // at or below its first timestamp, above its last, or inside the first
-// TGL_NODE_INLINE timestamps (held in the record); otherwise a binary search
-// of the rest of the run, which then holds an entry at or above t (the last
+// TGL_NODE_INLINE timestamps (held in the record); otherwise the edge is
+// looked for in the run, which then holds an entry at or above t (the last
 // one).  A neighbour id outside [0, N) gets {0, 0}.  With set_hint, the
 // entry's TGL_NBR_FIRST bit is written from the span (hi == lo: no entry of
-// v below t) over a clear bit.  Wavefront-tiled like emit_kernel, so that
-// each lane's record loads for its kEmitPerLane entries are in flight
-// together.
+// v below t) over a clear bit.
+//
+// What bounds it is random 128-byte lines: an entry's record, and for a
+// long run its directory cell and the stretch of timestamps there.  Each is
+// fetched once, whole, by neighbouring lanes:
+//   phase 1, 64 entries per wavefront, 8 lanes per entry and round, the eight
+//     rounds' loads in flight together: lane i of a group reads the i-th 16
+//     bytes of the record, the counts below t are added across the group, and
+//     lane i keeps the answer of round i, which is its own entry's;
+//   phase 2, one lane per entry left: its cell in the run's directory (DIR);
+//   phase 3, 8 lanes per entry left: the stretch of timestamps.
+// One lane per entry, reading its record in eight 16-byte loads and searching
+// the run by halves, fetched a record's line up to eight times over (64
+// lanes' lines do not stay in a 32 KB L1) and took a dependent load per
+// halving.  Histories of 200M entries of a power-law graph, most of whose
+// neighbours have runs longer than a record, 26.0 -> 9.0 ms; of 400M entries
+// of a citation graph, most of them decided by a record, 15.2 -> 14.9 ms: 51
+// GB of random record lines at 3.4 TB/s, where a sum over 4 GB reads 4.0.
+template <bool DIR>
 __global__ __launch_bounds__(kBlock) void hist_kernel(int4 *__restrict__ ent, const float *__restrict__ ts,
                                                       int64_t M, const int4 *__restrict__ nodes, int64_t N,
-                                                      uint2 *__restrict__ hist, bool set_hint) {
+                                                      const float *__restrict__ tsx, uint32_t nx,
+                                                      const uint2 *__restrict__ dir, uint2 *__restrict__ hist,
+                                                      bool set_hint) {
+    constexpr int G = 8;
+    constexpr uint32_t X = TGL_INDEX_STRIDE;
+    static_assert(sizeof(tgl_node) == G * 16, "a record is one 16-byte word per lane of a group");
     int2 *const head = reinterpret_cast<int2 *>(ent);        // (nbr, ts) of each 16-byte entry
+    __shared__ RunShape s_run[kWaves][kWave];                // entries left after phase 1, packed
+    __shared__ float s_t[kWaves][kWave];
+    __shared__ uint2 s_range[kWaves][DIR ? kWave : 1];       // DIR: where the edge lies; x == y: found
+    __shared__ uint32_t s_hi[kWaves][kWave];
     const uint32_t um = static_cast<uint32_t>(M);
     const int lane = lane_id();
-    const int64_t wave = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) / kWave;
-    const int64_t waves = static_cast<int64_t>(gridDim.x) * (kBlock / kWave);
-    for (int64_t base = wave * kEmitSpan; base < M; base += waves * kEmitSpan) {
-        int2 e[kEmitPerLane];
-#pragma unroll
-        for (int j = 0; j < kEmitPerLane; j++) {
-            const int64_t p = base + j * kWave + lane;
-            e[j] = head[2 * (p < M ? p : M - 1)];
-        }
-        int4 h[kEmitPerLane];
-#pragma unroll
-        for (int j = 0; j < kEmitPerLane; j++) {
-            const uint32_t x = static_cast<uint32_t>(e[j].x) & TGL_NBR_MASK;
-            h[j] = nodes[static_cast<int64_t>(static_cast<int64_t>(x) < N ? x : 0u) * 8];   // record 0 stands in
-        }
-#pragma unroll
-        for (int j = 0; j < kEmitPerLane; j++) {
-            const int64_t p = base + j * kWave + lane;
-            if (p >= M) continue;
-            const uint32_t x = static_cast<uint32_t>(e[j].x) & TGL_NBR_MASK;
-            const float t = __int_as_float(e[j].y);
-            uint32_t lo = 0, hi = 0;
-            if (static_cast<int64_t>(x) < N) {
-                uint32_t a = static_cast<uint32_t>(h[j].x), b = static_cast<uint32_t>(h[j].y);
-                a = a > um ? um : a;
-                b = b < a ? a : (b > um ? um : b);
-                lo = a;
-                if (!(__int_as_float(h[j].z) < t)) {
-                    hi = a;                               // nothing below t (or t is NaN)
-                } else if (__int_as_float(h[j].w) < t) {
-                    hi = b;                               // the whole run
-                } else {
-                    const int4 *const rec = nodes + static_cast<int64_t>(x) * 8;
-                    uint32_t c = 0;                       // inline timestamps below t (+inf past the run)
-#pragma unroll
-                    for (int q = 1; q <= TGL_NODE_INLINE / 4; q++) {
-                        const int4 w = rec[q];
-                        c += (__int_as_float(w.x) < t) + (__int_as_float(w.y) < t) + (__int_as_float(w.z) < t) +
-                             (__int_as_float(w.w) < t);
-                    }
-                    if (c < TGL_NODE_INLINE || b - a <= TGL_NODE_INLINE) {
-                        hi = a + c;
-                    } else {
-                        // the first position of [a + TGL_NODE_INLINE, b) with ts >= t;
-                        // ts[b - 1] (the last timestamp) is one
-                        uint32_t l = a + TGL_NODE_INLINE, r = b - 1;
-                        while (l < r) {
-                            const uint32_t m = l + (r - l) / 2;
-                            if (ts[m] < t) l = m + 1;
-                            else r = m;
-                        }
-                        hi = l;
-                    }
-                }
-                if (set_hint && hi == lo) head[2 * p].x = static_cast<int>(x | TGL_NBR_FIRST);
+    const int gl = lane & (G - 1);
+    const int gw = lane / G;
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+    const int64_t waves = static_cast<int64_t>(gridDim.x) * kWaves;
+    for (int64_t base = (static_cast<int64_t>(blockIdx.x) * kWaves + w) * kWave; base < M; base += waves * kWave) {
+        // ---- phase 1 ----
+        const int64_t p = base + lane;
+        const int2 e = head[2 * (p < M ? p : M - 1)];
+        const uint32_t x = static_cast<uint32_t>(e.x) & TGL_NBR_MASK;
+        const float t = __int_as_float(e.y);
+        const uint32_t xr = static_cast<int64_t>(x) < N ? x : 0u;   // record 0 stands in
+        int4 rec[G];
+        static_for<G>([&](auto ic) {
+            constexpr int I = decltype(ic)::value;
+            rec[I] = nodes[static_cast<int64_t>(static_cast<uint32_t>(bcast8<I>(static_cast<int>(xr)))) * G + gl];
+        });
+        uint32_t a = 0, b = 0, c = 0;              // this lane's entry: its run, inline timestamps below t
+        float first = 0.0f, last = 0.0f;
+        static_for<G>([&](auto ic) {
+            constexpr int I = decltype(ic)::value;
+            const float ti = __int_as_float(bcast8<I>(e.y));
+            const int4 r = rec[I];
+            const int below = (__int_as_float(r.x) < ti) + (__int_as_float(r.y) < ti) + (__int_as_float(r.z) < ti) +
+                              (__int_as_float(r.w) < ti);
+            const int sum = sum8(gl == 0 ? 0 : below);     // lane 0 holds the run's bounds
+            const int ra = bcast8<0>(r.x), rb = bcast8<0>(r.y), rf = bcast8<0>(r.z), rl = bcast8<0>(r.w);
+            if (gl == I) {
+                a = static_cast<uint32_t>(ra);
+                b = static_cast<uint32_t>(rb);
+                first = __int_as_float(rf);
+                last = __int_as_float(rl);
+                c = static_cast<uint32_t>(sum);
             }
-            hist[p] = make_uint2(lo, hi);
+        });
+        a = a > um ? um : a;
+        b = b < a ? a : (b > um ? um : b);
+        const bool in = p < M && static_cast<int64_t>(x) < N;
+        uint32_t hi = a;
+        bool need = false;
+        if (first < t) {                            // else nothing below t (or t is NaN)
+            if (last < t) hi = b;                   // the whole run
+            else if (c < TGL_NODE_INLINE || b - a <= TGL_NODE_INLINE) hi = a + c;
+            else need = in;
+        }
+        const uint64_t mask = __ballot(need);
+        if (mask != 0) {
+            // ---- phase 2: the entries left, packed ----
+            const int r = rank_below(mask);
+            if (need) {
+                s_run[w][r] = RunShape{a, b, first, last};
+                s_t[w][r] = t;
+                if constexpr (DIR) {
+                    // the edge lies in the directory's cell of t (tgl_cell): at its first
+                    // position pos, or when t is above that timestamp, past it
+                    // and at or before the next cell's
+                    const uint32_t ja = a / X + (a % X != 0);
+                    const uint32_t K = b / X + (b % X != 0) - ja;
+                    uint32_t l = a + TGL_NODE_INLINE, h = b;
+                    if (K > 0) {
+                        const uint32_t kc = dir_cell(t, first, last, dir_scale(first, last, K), K);
+                        const uint2 c0 = dir[ja + kc];
+                        const uint32_t c1 = kc + 1 < K ? dir[ja + kc + 1].x : b;
+                        const bool past = t > __uint_as_float(c0.y);
+                        const uint32_t dl = past ? c0.x + 1 : c0.x, dh = past ? c1 : c0.x;
+                        l = dl < l ? l : (dl > b ? b : dl);
+                        h = dh < l ? l : (dh > b ? b : dh);
+                    }
+                    s_range[w][r] = make_uint2(l, h);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // ---- phase 3: 8 lanes per entry ----
+            const int left = __popcll(mask);
+            for (int i0 = 0; i0 < left; i0 += kWave / G) {
+                const int i = i0 + gw;
+                if (i >= left) continue;            // group-uniform
+                const RunShape rs = s_run[w][i];
+                const float vt[1] = {s_t[w][i]};
+                const bool act[1] = {true};
+                uint32_t out[1];
+                if constexpr (DIR) {
+                    const uint2 rg = s_range[w][i];
+                    const uint32_t lo0[1] = {rg.x}, hi0[1] = {rg.y};
+                    count_below_ranges<G, 1>(ts, um, tsx, nx, lo0, hi0, vt, act, out, gl);
+                } else {
+                    count_below_n<G, 1, false>(ts, um, tsx, nx, nullptr, nullptr, rs.a, rs.b, rs, vt, act, out, gl);
+                }
+                if (gl == 0) s_hi[w][i] = out[0];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (need) hi = s_hi[w][r];
+        }
+        if (p < M) {
+            if (!in) {
+                a = 0;
+                hi = 0;
+            } else if (set_hint && hi == a) {
+                head[2 * p].x = static_cast<int>(x | TGL_NBR_FIRST);
+            }
+            hist[p] = make_uint2(a, hi);
         }
     }
 }
@@ -828,6 +926,15 @@ unsigned grid_for(int64_t n, int64_t cap = 1 << 16) {
     return static_cast<unsigned>(b);
 }
 
+// Histories of M > 0 entries, searching long runs from their directories
+// when there are any (written before), else on the search index.
+void launch_hist(int4 *ent, const float *ts, int64_t M, const int4 *nodes, int64_t N, const float *tsx,
+                 const uint2 *dir, uint2 *hist, bool set_hint, hipStream_t st) {
+    const uint32_t nx = static_cast<uint32_t>(tgl_index_len(M));
+    if (dir) hist_kernel<true><<<grid_for(M), kBlock, 0, st>>>(ent, ts, M, nodes, N, tsx, nx, dir, hist, set_hint);
+    else hist_kernel<false><<<grid_for(M), kBlock, 0, st>>>(ent, ts, M, nodes, N, tsx, nx, dir, hist, set_hint);
+}
+
 }  // namespace
 }  // namespace tgl
 
@@ -967,15 +1074,15 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
         const int64_t L = tgl_index_len(M);
         index_kernel<<<grid_for(L), kBlock, 0, st>>>(ts_out, L, ts_index_out);
     }
-    if (hist_out)
-        hist_kernel<<<grid_for((M + kEmitPerLane - 1) / kEmitPerLane), kBlock, 0, st>>>(
-            reinterpret_cast<int4 *>(entries), ts_out, M, reinterpret_cast<const int4 *>(nodes_out), num_nodes,
-            reinterpret_cast<uint2 *>(hist_out), true);
     if (dir_out) {
         const int64_t L = tgl_index_len(M);
         dir_kernel<<<grid_for(L), kBlock, 0, st>>>(indptr, ts_out, reinterpret_cast<const int4 *>(nodes_out),
                                                    num_nodes, M, L, reinterpret_cast<uint2 *>(dir_out));
     }
+    if (hist_out)
+        launch_hist(reinterpret_cast<int4 *>(entries), ts_out, M, reinterpret_cast<const int4 *>(nodes_out), num_nodes,
+                    ts_index_out, reinterpret_cast<const uint2 *>(dir_out), reinterpret_cast<uint2 *>(hist_out), true,
+                    st);
     return launch_status();
 }
 
@@ -1008,15 +1115,14 @@ tgl_status tgl_tcsr_nodes(const int64_t *indptr, const float *ts, int64_t num_no
         const int64_t L = tgl_index_len(num_entries);
         index_kernel<<<grid_for(L), kBlock, 0, st>>>(ts, L, ts_index);
     }
-    if (hist && num_entries > 0)
-        hist_kernel<<<grid_for((num_entries + kEmitPerLane - 1) / kEmitPerLane), kBlock, 0, st>>>(
-            reinterpret_cast<int4 *>(entries), ts, num_entries, reinterpret_cast<const int4 *>(nodes), num_nodes,
-            reinterpret_cast<uint2 *>(hist), false);
     if (dir && num_entries > 0) {
         const int64_t L = tgl_index_len(num_entries);
         dir_kernel<<<grid_for(L), kBlock, 0, st>>>(indptr, ts, reinterpret_cast<const int4 *>(nodes), num_nodes,
                                                    num_entries, L, reinterpret_cast<uint2 *>(dir));
     }
+    if (hist && num_entries > 0)
+        launch_hist(reinterpret_cast<int4 *>(entries), ts, num_entries, reinterpret_cast<const int4 *>(nodes), num_nodes,
+                    ts_index, reinterpret_cast<const uint2 *>(dir), reinterpret_cast<uint2 *>(hist), false, st);
     return launch_status();
 }
 
