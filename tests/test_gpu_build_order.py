@@ -1,0 +1,62 @@
+"""T-CSR builds of edge lists in time order, which skip the sort by time,
+against the oracle: times that are all different, in ties of a few, in ties
+that span tiles of the merge (2048 edges) and all equal, with -0 beside +0 and
+infinities; sizes around a tile; directed and undirected; both sort-key
+layouts (with 2^22 nodes and signed times the fields need more than 64 bits).
+A list with one edge out of order takes the full sort."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2203_14883_amd as P
+from gpu_util import announce, require_gpu, tcsr_to_host, upload
+
+pytestmark = pytest.mark.gpu
+
+
+def _times(rng, kind, m):
+    if kind == "distinct":
+        t = np.sort(rng.standard_normal(m).astype(np.float32) * 1e6)
+    elif kind == "few":
+        t = np.sort(rng.integers(-m // 6, m // 6 + 1, m)).astype(np.float32)
+    elif kind == "long":
+        t = np.sort(rng.integers(-1, 2, m)).astype(np.float32)
+        z = np.flatnonzero(t == 0)
+        t[z[::3]] = -0.0
+    elif kind == "equal":
+        t = np.full(m, 3.0, np.float32)
+    else:
+        t = np.sort(rng.integers(0, 40, m)).astype(np.float32)
+        t[: m // 3] = -np.inf
+        t[m - m // 3:] = np.inf
+    return t
+
+
+@pytest.mark.parametrize("nodes", [37, 1 << 22])
+@pytest.mark.parametrize("kind", ["distinct", "few", "long", "equal", "infinite"])
+def test_chronological(kind, nodes):
+    require_gpu()
+    rng = np.random.default_rng(5)
+    for m in (1, 2, 3, 65, 2047, 2048, 2049, 4097, 20_011) if nodes == 37 else (2, 20_011):
+        src = rng.integers(0, nodes, m).astype(np.int32)
+        dst = np.where(rng.random(m) < 0.1, src, rng.integers(0, nodes, m)).astype(np.int32)   # self-loops among them
+        ts = _times(rng, kind, m)
+        eid = rng.integers(-5, 1 << 40, m) if m % 2 else None
+        for und in (True, False):
+            for late in (False, True):
+                t = ts.copy()
+                if late:
+                    if m < 2:
+                        continue
+                    t[m - 1] = t[0] - np.float32(1)
+                    if not t[m - 1] < t[m - 2]:
+                        continue
+                announce("%s nodes %d edges %d undirected=%s late=%s" % (kind, nodes, m, und, late))
+                g = P.tcsr_build(upload(src), upload(dst), upload(t), None if eid is None else upload(eid), nodes, und,
+                                 hist=nodes == 37)
+                got = tcsr_to_host(g)
+                want = oracle.build_tcsr(src, dst, t, eid, nodes, und)
+                assert np.array_equal(got.indptr, want.indptr)
+                assert np.array_equal(got.nbr, want.nbr)
+                assert np.array_equal(got.eid, want.eid)
+                assert np.array_equal(got.ts.view(np.int32), want.ts.view(np.int32))
