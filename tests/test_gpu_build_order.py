@@ -52,8 +52,7 @@ def test_chronological(kind, nodes):
                     if not t[m - 1] < t[m - 2]:
                         continue
                 announce("%s nodes %d edges %d undirected=%s late=%s" % (kind, nodes, m, und, late))
-                g = P.tcsr_build(upload(src), upload(dst), upload(t), None if eid is None else upload(eid), nodes, und,
-                                 hist=nodes == 37)
+                g = P.tcsr_build(upload(src), upload(dst), upload(t), None if eid is None else upload(eid), nodes, und)
                 got = tcsr_to_host(g)
                 want = oracle.build_tcsr(src, dst, t, eid, nodes, und)
                 assert np.array_equal(got.indptr, want.indptr)
