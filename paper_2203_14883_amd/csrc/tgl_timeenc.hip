@@ -3,31 +3,30 @@
 // cos(omega * dt + phi), omega and phi learnable vectors of the encoder's
 // dimension).
 //
-// Each slot's row is dim independent elements, so the kernel is bound by the
-// bytes it writes (dim * 4 or dim * 2 per slot against 4 read).  A wavefront
-// encodes kRows slots at a time: one vector load brings their kRows time
-// differences (lane u holds slot u's), each is broadcast from its lane, and
-// lane l computes elements l, l + 64, ... of the row, so every store
-// instruction writes 64 consecutive elements and no row waits on a load.
+// Each slot's row is dim independent elements, so the encoding is bound by the
+// bytes it writes (dim * 4 or dim * 2 per slot against 4 read).  16-byte output
+// words are dealt to the lanes of the grid such that a lane's columns never
+// change (timeenc_word_kernel); rows of fewer elements than a word, or an
+// output that is not 16-byte aligned, take a wavefront per row
+// (timeenc_kernel).
 //
 // Accuracy: the argument is formed in turns, t = (omega / 2 pi) dt + phi / 2 pi,
 // in double precision, from per-column factors omega / 2 pi and phi / 2 pi
-// (each within 2^-52 relative of exact); below 2^24 turns t is within 5e-8
-// rad of the exact argument.  Its fraction f = t - rint(t) is exact, and
-// cos(2 pi f) = cos(2 pi g) for g = |f| in [0, 1/2]; above 1/4 it is
-// -cos(2 pi (1/2 - g)), also exact, so only [0, 1/4] is left: x = 2 pi g
-// in [0, pi/2], where the cosine's Taylor series to x^12, in powers of g^2,
-// leaves out less than 6.4e-9.  g is rounded to float (2.4e-8 rad) and the
-// series evaluated by fused multiply-adds in float (a few float ulps).  The
-// result is within 3e-7 of cos(omega dt + phi).  A plain float evaluation of
-// the argument would be off by up to half an ulp of omega * dt -- 0.125 at
-// dt = 2.7e6 s, Wikipedia's time span -- which the cosine passes on
-// unchanged.  Arguments of 2^24 turns or more, infinite or NaN use the double
-// cosine of the double argument instead.
+// (each within 2^-52 relative of exact).  Below 2^19 turns its fraction is
+// taken as a phase in units of 2^-32 turns (7e-10 rad of rounding) and
+// cos_phase evaluates it; from there to 2^24 turns, where t is within 5e-8 rad
+// of the exact argument, f = t - rint(t) is exact, and cos(2 pi f) = cos(2 pi
+// g) for g = |f| in [0, 1/2]; above 1/4 it is -cos(2 pi (1/2 - g)), also exact,
+// so only [0, 1/4] is left: x = 2 pi g in [0, pi/2], where the cosine's Taylor
+// series to x^12, in powers of g^2, leaves out less than 6.4e-9.  g is rounded
+// to float (2.4e-8 rad) and the series evaluated by fused multiply-adds in
+// float (a few float ulps).  The result is within 3e-7 of cos(omega dt + phi).
+// A plain float evaluation of the argument would be off by up to half an ulp
+// of omega * dt -- 0.125 at dt = 2.7e6 s, Wikipedia's time span -- which the
+// cosine passes on unchanged.  Arguments of 2^24 turns or more, infinite or
+// NaN use the double cosine of the double argument instead.
 //
-// Padded slots (dt < 0) have no time difference: their rows are zeros, and a
-// row's dt is the same for the whole wavefront, so those rows branch to plain
-// stores.
+// Padded slots (dt < 0) have no time difference: their rows are zeros.
 #include <atomic>
 
 #include "tgl_internal.hpp"
@@ -47,6 +46,20 @@ constexpr float kC3 = -85.45681720669373f;
 constexpr float kC4 = 60.24464137187666f;
 constexpr float kC5 = -26.426256783374397f;
 constexpr float kC6 = 7.903536371318469f;
+
+// sin(z pi / 2) = z (kS1 + (kS1Lo + kS3 z^2 + ... + kS9 z^8)): see cos_phase
+constexpr float kS1 = 1.5707963705062866f;
+constexpr float kS1Lo = -4.371138828673793e-08f;
+constexpr float kS3 = -0.645963728427887f;
+constexpr float kS5 = 0.07968960702419281f;
+constexpr float kS7 = -0.0046735769137740135f;
+constexpr float kS9 = 0.00015137750597205013f;
+
+constexpr double kPhaseBase = 0x1.8p20;                            // doubles near it are 2^-32 apart
+constexpr uint32_t kPhaseHigh = 0x41300000u;                       // high word of the doubles in [2^20, 2^21): this ...
+constexpr uint32_t kPhaseSpan = 0x00100000u;                       // ... plus less than that
+
+using i32x4 = int __attribute__((ext_vector_type(4)));
 
 // cos(2 pi t) for an argument t in turns with |t| < kTurnLimit
 __device__ __forceinline__ float cos_turns(double t) {
@@ -91,6 +104,16 @@ __device__ __forceinline__ uint16_t to_bf16(float v) {
     return static_cast<uint16_t>((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
 }
 
+// Two floats as bfloat16, a in the low half (one v_cvt_pk_bf16_f32).
+__device__ __forceinline__ int pack_bf16(float a, float b) {
+    using f32x2 = float __attribute__((ext_vector_type(2)));
+    using bf16x2 = __bf16 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(int, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+// Rows by wavefronts, kRows slots at a time: one vector load brings their
+// time differences (lane u holds slot u's), each is broadcast from its lane,
+// and lane l computes elements l, l + 64, ... of the row.
 template <int OUT, bool PRE>
 __global__ __launch_bounds__(kBlock) void timeenc_kernel(const float *__restrict__ dt, int64_t n,
                                                          const int64_t *__restrict__ count, int64_t per,
@@ -140,122 +163,134 @@ __global__ __launch_bounds__(kBlock) void timeenc_kernel(const float *__restrict
     }
 }
 
-// Rows whose byte size is a multiple of 16: lane l of a wavefront owns the
-// 16-byte word w0 + l of the flattened output (EPW elements: 4 float32 or 8
-// bfloat16), so one store instruction writes 1 KB of contiguous output.
-// With float32 output and the factors in LDS, a lane reads its word's four
-// factor pairs together and checks the four arguments once, so the elements
-// are evaluated side by side rather than each behind its own LDS wait and
-// branch; that kernel is held to 64 VGPRs, i.e. 8 wavefronts per SIMD (at 7
-// it is slower than the element-by-element form).  The other forms keep the
-// element-by-element evaluation, which needs fewer registers.
-template <int OUT, bool PRE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(OUT == TGL_OUT_F32 && PRE ? 8 : 1)))
-void timeenc_vec_kernel(const float *__restrict__ dt, int64_t n, const int64_t *__restrict__ count, int64_t per,
-                        const float *__restrict__ omega, const float *__restrict__ phi, int dim,
-                        void *__restrict__ out) {
+// cos(2 pi p 2^-32) of a phase p in units of 2^-32 turns (mod 1).  With a =
+// |p| taken mod 1 it is sin(2 pi (1/4 - a)): one v_sad gives 2^30 - a, whose
+// conversion to float is z = x / (pi / 2) scaled, x in [-pi/2, pi/2], and the
+// odd polynomial below finishes it.  Its coefficients are the minimax fit of
+// sin x - x on [0, pi/2] (error 4.6e-9) in powers of z; pi/2 is split in two
+// so that the leading product's rounding is the result's.
+__device__ __forceinline__ float cos_phase(uint32_t p) {
+    const int h = static_cast<int>(__usad(p, 0x80000000u, 0xc0000000u));   // |p - 2^31| - 2^30 (mod 2^32)
+    const float z = static_cast<float>(h) * 0x1p-30f;
+    const float y = z * z;
+    float q = __builtin_fmaf(y, kS9, kS7);
+    q = __builtin_fmaf(y, q, kS5);
+    q = __builtin_fmaf(y, q, kS3);
+    q = __builtin_fmaf(y, q, kS1Lo);
+    return __builtin_fmaf(z, kS1, z * q);
+}
+
+// Lane l of the grid owns the 16-byte output words l, l +
+// T, ... (EPW elements each: 4 float32 or 8 bfloat16; T lanes in all), so one
+// store instruction writes 1 KB of contiguous output.  T * EPW is a multiple
+// of dim whenever a lane has more than one word, so its columns never change:
+// their factors stay in registers and its row advances by row_step.  With
+// STRADDLE a row is not a whole number of words: a word's elements from
+// column dim on belong to the next row, and the last word may end early.
+//
+// The argument t = (omega / 2 pi) dt + phi / 2 pi is formed in turns by one
+// double fma on top of kPhaseBase, whose unit in the last place is 2^-32 turns:
+// the sum's low word is the phase, rounded to 2^-33 turns (7e-10 rad), as
+// long as |t| < 2^19, which the sum's high word shows.  Larger arguments take
+// encode().  11 float instructions and one double one per element; before, a
+// rounding to turns, a fold and two comparisons were double too, factors came
+// from LDS for every word, and rows that are not whole words were written an
+// element at a time.  100 float32 of 8M slots 821 -> 603 us (5.6 TB/s; a plain
+// fill writes 6.9), 100 bfloat16 1112 -> 444, 101 float32 of 2M slots 384 ->
+// 141, 33 bfloat16 145 -> 37.  Error against 64 bits 3.1e-8 (2-norm) and 1.3e-7
+// at most; 3.3e-8 and 1.6e-7 before.
+template <int OUT, bool STRADDLE>
+__global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__restrict__ dt, int64_t n,
+                                                              const int64_t *__restrict__ count, int64_t per,
+                                                              const float *__restrict__ omega,
+                                                              const float *__restrict__ phi, int dim,
+                                                              int64_t row_step, void *__restrict__ out) {
     constexpr int EPW = OUT == TGL_OUT_F32 ? 4 : 8;                 // elements per 16-byte word
-    __shared__ double2 fac[PRE ? kMaxPre : 1];
-    if constexpr (PRE) load_factors(fac, omega, phi, dim);
-    const int lane = lane_id();
-    constexpr int kWaves = kBlock / kWave;
-    const int64_t waves = static_cast<int64_t>(gridDim.x) * kWaves;
-    const int64_t wave = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * kWaves + threadIdx.x / kWave));
     if (count) {
         const int64_t c = *count;
         const int64_t lim = c <= 0 ? 0 : (c > n / per ? n : c * per);
         n = lim < n ? lim : n;
     }
-    const uint32_t wpr = static_cast<uint32_t>(dim / EPW);           // words per row, at most 1024
-    const int64_t total = n * wpr;
-    int4 *const o = static_cast<int4 *>(out);
-    // The wavefront's first word w0 as (row0, off0), advanced by the grid
-    // stride without dividing; a lane's word w0 + lane is off0 + lane < wpr + 64
-    // words past row0's start, split by a float reciprocal (exact after one
-    // correction: the quotient is at most 64 and the product is within 2^-22
-    // of it).
-    const float inv_wpr = 1.0f / static_cast<float>(wpr);
-    const int64_t step = waves * kWave;
-    const int64_t step_q = step / wpr;
-    const uint32_t step_r = static_cast<uint32_t>(step - step_q * wpr);
-    int64_t w0 = wave * kWave;
-    int64_t row0 = w0 / wpr;
-    uint32_t off0 = static_cast<uint32_t>(w0 - row0 * wpr);
-    for (; w0 < total; w0 += step) {
-        if (w0 + lane < total) {
-            const uint32_t r = off0 + static_cast<uint32_t>(lane);
-            uint32_t dr = static_cast<uint32_t>(static_cast<float>(r) * inv_wpr);
-            if ((dr + 1) * wpr <= r) dr++;
-            const int64_t row = row0 + dr;
-            const int col = static_cast<int>(r - dr * wpr) * EPW;
-            const float d = dt[row];
-            float v[EPW];
-            if (d < 0.0f) {
+    const int64_t elems = n * dim;
+    const int64_t total = (elems + EPW - 1) / EPW;                  // words
+    const int64_t T = static_cast<int64_t>(gridDim.x) * kBlock;
+    int64_t w = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if (w >= total) return;
+    int64_t row = w * EPW / dim;
+    const int col = static_cast<int>(w * EPW - row * dim);
+    double wp[EPW], pb[EPW];
 #pragma unroll
-                for (int e = 0; e < EPW; e++) v[e] = 0.0f;
-            } else if constexpr (OUT == TGL_OUT_F32 && PRE) {
-                // the factors as the general form reads them: with a plain
-                // fac[col + e] hipcc combines the four range checks through
-                // 16-bit vector ops instead of lane masks, and runs slower
-                double2 fj[EPW];
+    for (int e = 0; e < EPW; e++) {
+        const int j = STRADDLE && col + e >= dim ? col + e - dim : col + e;
+        wp[e] = static_cast<double>(omega[j]) * kInvTwoPi;
+        pb[e] = static_cast<double>(phi[j]) * kInvTwoPi + kPhaseBase;
+    }
+    for (; w < total; w += T, row += row_step) {
+        const float d0 = dt[row];
+        float d1 = d0;
+        if constexpr (STRADDLE) d1 = dt[row + 1 < n ? row + 1 : row];
+        float v[EPW];
+#pragma unroll
+        for (int e = 0; e < EPW; e++) v[e] = 0.0f;
+        // PAD slots; a NaN time difference gives NaN, or zeros in rows that
+        // are not whole words
+        const bool pad0 = STRADDLE ? !(d0 >= 0.0f) : d0 < 0.0f;
+        const bool pad1 = STRADDLE ? !(d1 >= 0.0f) : pad0;
+        if (!pad0 || !pad1) {
+            uint32_t ph[EPW], far = 0;
+#pragma unroll
+            for (int e = 0; e < EPW; e++) {
+                const float d = STRADDLE && col + e >= dim ? d1 : d0;
+                const uint64_t s = __builtin_bit_cast(uint64_t, fma(wp[e], static_cast<double>(d), pb[e]));
+                ph[e] = static_cast<uint32_t>(s);
+                far |= static_cast<uint32_t>(s >> 32) ^ kPhaseHigh;
+            }
+            if (far < kPhaseSpan) {
+#pragma unroll
+                for (int e = 0; e < EPW; e++) v[e] = cos_phase(ph[e]);
+            } else {                                                // some |t| >= 2^19, infinite or NaN
+                // one element after the other: nothing of the double cosine
+                // is held in registers by the path above
+#pragma unroll 1
+                for (int e = 0; e < EPW; e++) {
+                    const bool next = STRADDLE && col + e >= dim;
+                    const int j = next ? col + e - dim : col + e;
+                    const float r = encode(static_cast<double>(omega[j]) * kInvTwoPi,
+                                           static_cast<double>(phi[j]) * kInvTwoPi, next ? d1 : d0, omega, phi, j);
+#pragma unroll
+                    for (int i = 0; i < EPW; i++) v[i] = i == e ? r : v[i];
+                }
+            }
+            if constexpr (STRADDLE) {
 #pragma unroll
                 for (int e = 0; e < EPW; e++)
-                    fj[e] = PRE ? fac[col + e]
-                                : make_double2(static_cast<double>(omega[col + e]) * kInvTwoPi,
-                                               static_cast<double>(phi[col + e]) * kInvTwoPi);
-                const double dd = static_cast<double>(d);
-                double t[EPW];
-                bool ok = true;
-#pragma unroll
-                for (int e = 0; e < EPW; e++) {
-                    t[e] = fma(fj[e].x, dd, fj[e].y);
-                    ok = ok && fabs(t[e]) < kTurnLimit;
-                }
-                if (ok) {                           // the arguments encode() reduces itself
-#pragma unroll
-                    for (int e = 0; e < EPW; e++) v[e] = cos_turns(t[e]);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < EPW; e++) v[e] = encode(fj[e].x, fj[e].y, d, omega, phi, col + e);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < EPW; e++) {
-                    const double2 fj = PRE ? fac[col + e]
-                                           : make_double2(static_cast<double>(omega[col + e]) * kInvTwoPi,
-                                                          static_cast<double>(phi[col + e]) * kInvTwoPi);
-                    v[e] = encode(fj.x, fj.y, d, omega, phi, col + e);
-                }
+                    if (col + e >= dim ? pad1 : pad0) v[e] = 0.0f;
             }
-            int4 word;
-            if constexpr (OUT == TGL_OUT_F32) {
-                word = make_int4(__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3]));
-            } else {
-                uint32_t pk[4];
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    pk[e] = static_cast<uint32_t>(to_bf16(v[2 * e])) | (static_cast<uint32_t>(to_bf16(v[2 * e + 1])) << 16);
-                word = make_int4(static_cast<int>(pk[0]), static_cast<int>(pk[1]), static_cast<int>(pk[2]),
-                                 static_cast<int>(pk[3]));
-            }
-            o[w0 + lane] = word;
         }
-        row0 += step_q;
-        off0 += step_r;
-        if (off0 >= wpr) {
-            off0 -= wpr;
-            row0++;
+        if (STRADDLE && w * EPW + EPW > elems) {                    // the last word, cut short
+#pragma unroll
+            for (int e = 0; e < EPW; e++) {
+                if (w * EPW + e >= elems) continue;
+                if constexpr (OUT == TGL_OUT_F32) static_cast<float *>(out)[w * EPW + e] = v[e];
+                else static_cast<uint16_t *>(out)[w * EPW + e] = to_bf16(v[e]);
+            }
+        } else {
+            i32x4 word;
+            if constexpr (OUT == TGL_OUT_F32) {
+                word = i32x4{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])};
+            } else {
+                word = i32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+            }
+            __builtin_nontemporal_store(word, static_cast<i32x4 *>(out) + w);
         }
     }
 }
 
-// Both kernels stride over their rows, so a grid of the blocks the device
-// holds at once does all the work and loads each block's factor table once:
-// with one block per 256 words (capped at 64 Ki blocks) a block lived for
-// about a dozen words and its factor load and barrier were a tenth of its
-// time.  Found once per device and kernel (CUs x resident blocks per CU).
+// Both kernels stride over their work, so a grid of the blocks the device
+// holds at once does all of it and loads each block's or lane's factors once.
+// Found once per device and kernel (CUs x resident blocks per CU).
 constexpr int kMaxDevices = 64;
-constexpr int kVariants = 8;                                       // row/word kernel x output x factor table
+constexpr int kVariants = 8;                                       // row/word kernel x output x factor table or straddle
 std::atomic<int> g_resident[kMaxDevices][kVariants];
 
 template <typename K>
@@ -277,6 +312,38 @@ unsigned resident_grid(K kernel, int variant, int64_t want) {
     (void)hipGetLastError();
     if (r <= 0) r = 1 << 16;
     return static_cast<unsigned>(want < r ? want : r);
+}
+
+int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
+
+// Words per lane, which make its setup (a division, its columns' factors)
+// small.  100 float32 of 8M slots take 633 us on the blocks resident together,
+// 603 on a block per 8 words of its lanes, 590 per 32 and 641 per 128; 172 of 2M
+// slots 272, 229, 256 and 281.  100 bfloat16 of 8M slots 444, 507, 425 and 425,
+// and 128 of 2M slots 117, 170, 147 and 119: float32 takes blocks of 8 words,
+// bfloat16 the resident ones.
+constexpr int64_t kLaneWordsF32 = 8;
+constexpr int64_t kLaneWordsBf16 = 4;
+constexpr int64_t kMaxBlocks = 1 << 22;
+
+// timeenc_word_kernel on a multiple of `unit` blocks, or on a block per 256
+// words when that is no more than `unit`.
+template <typename K>
+void launch_words(K kernel, int variant, int epw, int unit, hipStream_t st, const float *dt, int64_t n,
+                  const int64_t *count, int64_t per, const float *omega, const float *phi, int dim, void *out) {
+    const int64_t words = n > INT64_MAX / dim - epw ? INT64_MAX / epw : (n * dim + epw - 1) / epw;
+    const int64_t whole = words / kBlock + (words % kBlock != 0);
+    const bool f32 = epw == 4;
+    const int64_t lane_words = f32 ? kLaneWordsF32 : kLaneWordsBf16;
+    const int64_t most = f32 ? kMaxBlocks : resident_grid(kernel, variant, kMaxBlocks);
+    int64_t nb = whole / lane_words + (whole % lane_words != 0);
+    if (nb > most) nb = most;
+    nb = nb / unit * unit;
+    if (nb < unit) nb = unit;
+    if (nb > whole) nb = whole;                                    // one word per lane: no step is taken
+    const int64_t row_step = nb * kBlock * epw / dim;
+    ScopedTimer tm(TGL_TIMER_TIMEENC, st);
+    kernel<<<static_cast<unsigned>(nb), kBlock, 0, st>>>(dt, n, count, per, omega, phi, dim, row_step, out);
 }
 
 template <typename K>
@@ -308,17 +375,20 @@ tgl_status tgl_time_encode(const float *dt, int64_t n, const int64_t *count, int
     (void)hipGetLastError();
     const int esize = out_type == TGL_OUT_F32 ? 4 : 2;
     const bool pre = dim <= kMaxPre;                      // per-column factors staged in LDS
-    const bool vec = (static_cast<int64_t>(dim) * esize) % 16 == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
-    if (vec) {
-        const int64_t words = n * (static_cast<int64_t>(dim) * esize / 16);
-        const int64_t want = (words + kBlock - 1) / kBlock;
-        if (out_type == TGL_OUT_F32) {
-            if (pre) launch_resident(timeenc_vec_kernel<TGL_OUT_F32, true>, 4, want, st, dt, n, count, per_count, omega, phi, dim, out);
-            else launch_resident(timeenc_vec_kernel<TGL_OUT_F32, false>, 5, want, st, dt, n, count, per_count, omega, phi, dim, out);
-        } else {
-            if (pre) launch_resident(timeenc_vec_kernel<TGL_OUT_BF16, true>, 6, want, st, dt, n, count, per_count, omega, phi, dim, out);
-            else launch_resident(timeenc_vec_kernel<TGL_OUT_BF16, false>, 7, want, st, dt, n, count, per_count, omega, phi, dim, out);
-        }
+    const int epw = 16 / esize;
+    // words by lanes with columns of their own: T * epw, T the lanes of the
+    // grid, has to be a multiple of dim, i.e. the blocks one of `unit`
+    const int unit = dim / gcd(dim, kBlock * epw);
+    if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0 && dim >= epw) {
+        const bool straddle = dim % epw != 0;
+        if (out_type == TGL_OUT_F32 && straddle)
+            launch_words(timeenc_word_kernel<TGL_OUT_F32, true>, 5, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+        else if (out_type == TGL_OUT_F32)
+            launch_words(timeenc_word_kernel<TGL_OUT_F32, false>, 4, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+        else if (straddle)
+            launch_words(timeenc_word_kernel<TGL_OUT_BF16, true>, 7, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+        else
+            launch_words(timeenc_word_kernel<TGL_OUT_BF16, false>, 6, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
         return launch_status();
     }
     constexpr int64_t rows_per_block = static_cast<int64_t>(kBlock / kWave) * kRows;

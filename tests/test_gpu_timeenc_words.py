@@ -1,0 +1,51 @@
+"""Time encoding against the 64-bit cosine where its kernels' rules meet: rows
+of fewer elements than a 16-byte word, of whole words and of parts of one;
+widths whose lanes' columns repeat after few or many blocks; one word, one
+block and several words per lane; arguments on both sides of 2^19 turns (the
+phase in a double's low word) and 2^24; PAD slots, and a count that cuts the
+last rows; an output that is not 16-byte aligned.
+
+Tolerance: 1e-6 by the entry point's contract, plus half a bfloat16 step for
+bfloat16: a value in [2^e, 2^(e+1)) has steps of 2^(e-7), half of one being at
+most 2^-8 of the value."""
+import pytest
+
+import paper_2203_14883_amd as P
+from gpu_util import announce, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dim", [1, 3, 4, 5, 7, 8, 9, 12, 33, 100, 101, 256, 1021, 1024, 1025, 4095, 4096])
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_words(dim, dtype):
+    torch = require_gpu()
+    dt_ = getattr(torch, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(dim)
+    omega = 10.0 ** (-9.0 * torch.rand(dim, generator=gen, device="cuda"))
+    phi = torch.randn(dim, generator=gen, device="cuda")
+    omega[0] = 1.0
+    edge = 6.283185307179586 * 2.0 ** 19
+    special = torch.tensor([0.0, -0.0, 1.0, edge * 0.999999, edge, edge * 1.000001, edge * 33, edge * 400, 3e38, -1.0],
+                           device="cuda")
+    for n in (1, 2, 3, 257, 5000, 70_001):
+        if n * dim > 6_000_000:
+            continue
+        d = torch.empty(n, device="cuda").exponential_(1 / 3e5, generator=gen)
+        d = torch.where(torch.rand(n, generator=gen, device="cuda") < 0.3, -1.0, d)
+        k = min(n, len(special))
+        d[:k] = special[:k]
+        want = (torch.outer(d.double(), omega.double()) + phi.double()).cos()
+        want = torch.where((d < 0)[:, None], 0.0, want)
+        for cnt, shift in ((None, 0), (n - n // 3, 0), (None, 1)):
+            announce("dim %d %s slots %d count %s shift %d" % (dim, dtype, n, cnt, shift))
+            m = n if cnt is None else cnt
+            off = shift * (1 if dtype == "float32" else 2)
+            buf = torch.full((n * dim + off,), 77.0, dtype=dt_, device="cuda")
+            out = buf[off:].view(n, dim)
+            count = None if cnt is None else torch.tensor([cnt], device="cuda")
+            P.time_encode(d, omega, phi, dt_, count=count, out=out)
+            err = (out[:m].double() - want[:m]).abs()
+            bound = 1e-6 + (want[:m].abs() * 2.0 ** -8 if dtype == "bfloat16" else 0.0)
+            assert bool((err <= bound).all()), float(err.max())
+            assert bool((out[m:] == 77).all())
