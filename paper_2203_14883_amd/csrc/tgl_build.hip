@@ -420,6 +420,44 @@ __global__ __launch_bounds__(kBlock) void radix_upsweep_kernel(const uint64_t *_
     if (threadIdx.x < B) hist[static_cast<int64_t>(threadIdx.x) * ntiles + tile] = cnt[threadIdx.x];
 }
 
+// Exclusive scan of a small histogram in place, by one block: thread t owns
+// kSmallScanItems counts from t * kSmallScanItems on.  The reduce, totals and
+// apply kernels of the general scan take 10 us and two more launches for a
+// histogram of any size; this one 4 us for 10,000 counts.
+constexpr int kSmallScanThreads = 1024;
+constexpr int kSmallScanItems = 16;
+constexpr int64_t kSmallScanMax = int64_t(kSmallScanThreads) * kSmallScanItems;
+static_assert((1 << 7) % kSmallScanItems == 0, "a histogram is a multiple of the counts of one thread");
+using u32x4 = uint32_t __attribute__((ext_vector_type(4), aligned(4)));   // the workspace may be aligned to 4 bytes only
+
+__global__ __launch_bounds__(kSmallScanThreads) void hist_scan_small_kernel(uint32_t *__restrict__ hist, int n) {
+    __shared__ uint32_t lds[kSmallScanThreads / kWave];
+    const int base = static_cast<int>(threadIdx.x) * kSmallScanItems;
+    const bool in = base < n;
+    u32x4 v[kSmallScanItems / 4];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallScanItems / 4; i++) {
+        v[i] = *reinterpret_cast<const u32x4 *>(hist + (in ? base : 0) + 4 * i);
+        if (in) sum += v[i].x + v[i].y + v[i].z + v[i].w;
+    }
+    const uint32_t inc = wave_inclusive_sum(sum);
+    const int w = threadIdx.x / kWave;
+    if (lane_id() == kWave - 1) lds[w] = inc;
+    __syncthreads();
+    uint32_t run = inc - sum;
+#pragma unroll
+    for (int i = 0; i < kSmallScanThreads / kWave; i++)
+        if (i < w) run += lds[i];
+    if (!in) return;
+#pragma unroll
+    for (int i = 0; i < kSmallScanItems / 4; i++) {
+        const u32x4 c = v[i];
+        *reinterpret_cast<u32x4 *>(hist + base + 4 * i) = u32x4{run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z};
+        run += c.x + c.y + c.z + c.w;
+    }
+}
+
 // Stable scatter of one tile by its BITS-bit digit.  hist_off holds the
 // exclusive scan of hist (digit-major), i.e. where this tile's keys of digit
 // d start.
@@ -628,7 +666,9 @@ __global__ __launch_bounds__(kBlock) void pack_edges_kernel(const int32_t *__res
 // (packed layout) or from the edge list; with `first` (each node's
 // first_value) the entry's TGL_NBR_FIRST hint is set here.  Wavefront-tiled
 // like first_ts_kernel: each lane's gathers (neighbour, eid, first value) for
-// its kEmitPerLane entries are issued together.
+// its kEmitPerLane entries are issued together.  tsx, if not null, is the search
+// index: reading it back from ts_out is a pass over every line of it (0.32 ms
+// for 400M entries).
 template <class F>
 __global__ __launch_bounds__(kBlock) void emit_kernel(const uint64_t *__restrict__ keys,
                                                       const uint32_t *__restrict__ vals, int64_t M,
@@ -639,7 +679,7 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(const uint64_t *__restrict
                                                       const KeyLayout L, const F *__restrict__ first,
                                                       int64_t *__restrict__ indptr,
                                                       int4 *__restrict__ ent,
-                                                      float *__restrict__ ts_out) {
+                                                      float *__restrict__ ts_out, float *__restrict__ tsx) {
     const int lane = lane_id();
     const int64_t wave = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) / kWave;
     const int64_t waves = static_cast<int64_t>(gridDim.x) * (kBlock / kWave);
@@ -689,6 +729,7 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(const uint64_t *__restrict
             ent[p] = make_int4(static_cast<int>(vw), __float_as_int(t), static_cast<int>(static_cast<uint32_t>(e[j])),
                                static_cast<int>(static_cast<uint64_t>(e[j]) >> 32));
             ts_out[p] = t;
+            if (tsx && p % TGL_INDEX_STRIDE == 0) tsx[p / TGL_INDEX_STRIDE] = t;
             // owners are in [0, N) after validation; the clamps only bound the stores
             const int64_t uprev = p == 0 ? -1 : static_cast<int64_t>(key_node(L, prev[j]));
             const int64_t x1 = u < N ? u : N - 1;
@@ -1196,11 +1237,15 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
         else
             radix_upsweep_kernel<7><<<radix_grid(w.ntiles), kBlock, 0, st>>>(w.keys[cur], M, shift, w.hist,
                                                                                        w.ntiles);
-        scan_reduce_kernel<uint32_t><<<static_cast<unsigned>(sc_tiles), kBlock, 0, st>>>(
-            w.hist, nh, nullptr, w.partials);
-        launch_scan_partials(w.partials, sc_tiles, nullptr, st);
-        scan_apply_kernel<uint32_t, uint32_t><<<static_cast<unsigned>(sc_tiles), kBlock, 0, st>>>(
-            w.hist, w.hist, nh, nullptr, w.partials);
+        if (nh <= kSmallScanMax) {
+            hist_scan_small_kernel<<<1, kSmallScanThreads, 0, st>>>(w.hist, static_cast<int>(nh));
+        } else {
+            scan_reduce_kernel<uint32_t><<<static_cast<unsigned>(sc_tiles), kBlock, 0, st>>>(
+                w.hist, nh, nullptr, w.partials);
+            launch_scan_partials(w.partials, sc_tiles, nullptr, st);
+            scan_apply_kernel<uint32_t, uint32_t><<<static_cast<unsigned>(sc_tiles), kBlock, 0, st>>>(
+                w.hist, w.hist, nh, nullptr, w.partials);
+        }
         if (kb == 8)
             radix_downsweep_kernel<8><<<radix_grid(w.ntiles), kBlock, 0, st>>>(
                 w.keys[cur], w.vals[cur], w.keys[cur ^ 1], w.vals[cur ^ 1], M, shift, w.hist, w.ntiles);
@@ -1233,13 +1278,13 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
         fill_first_kernel<uint8_t><<<gn, kBlock, 0, st>>>(f, num_nodes);
         first_ts_kernel<uint8_t><<<gm, kBlock, 0, st>>>(w.keys[cur], M, L, f);
         emit_kernel<uint8_t><<<gm, kBlock, 0, st>>>(w.keys[cur], w.vals[cur], M, m0, src, dst, eid, edges, num_nodes, L, f,
-                                                    indptr, ent, ts_out);
+                                                    indptr, ent, ts_out, ts_index_out);
     } else if (first && fbytes == 2) {
         uint16_t *const f = static_cast<uint16_t *>(first);
         fill_first_kernel<uint16_t><<<gn, kBlock, 0, st>>>(f, num_nodes);
         first_ts_kernel<uint16_t><<<gm, kBlock, 0, st>>>(w.keys[cur], M, L, f);
         emit_kernel<uint16_t><<<gm, kBlock, 0, st>>>(w.keys[cur], w.vals[cur], M, m0, src, dst, eid, edges, num_nodes, L,
-                                                     f, indptr, ent, ts_out);
+                                                     f, indptr, ent, ts_out, ts_index_out);
     } else {
         float *const f = static_cast<float *>(first);
         if (f) {
@@ -1247,7 +1292,7 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
             first_ts_kernel<float><<<gm, kBlock, 0, st>>>(w.keys[cur], M, L, f);
         }
         emit_kernel<float><<<gm, kBlock, 0, st>>>(w.keys[cur], w.vals[cur], M, m0, src, dst, eid, edges, num_nodes, L, f,
-                                                  indptr, ent, ts_out);
+                                                  indptr, ent, ts_out, ts_index_out);
     }
     nodes_kernel<<<grid_for(num_nodes * 8), kBlock, 0, st>>>(indptr, ts_out, num_nodes, M,
                                                              reinterpret_cast<int4 *>(nodes_out), nullptr);
@@ -1255,10 +1300,6 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
         first_hint_kernel<<<grid_for(M), kBlock, 0, st>>>(reinterpret_cast<int4 *>(entries), ts_out, M,
                                                           reinterpret_cast<const float *>(nodes_out) + 2, 32,
                                                           num_nodes);
-    if (ts_index_out && M > 0) {
-        const int64_t L = tgl_index_len(M);
-        index_kernel<<<grid_for(L), kBlock, 0, st>>>(ts_out, L, ts_index_out);
-    }
     if (dir_out) {
         const int64_t L = tgl_index_len(M);
         dir_kernel<<<grid_for(L), kBlock, 0, st>>>(indptr, ts_out, reinterpret_cast<const int4 *>(nodes_out),

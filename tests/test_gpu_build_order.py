@@ -59,3 +59,18 @@ def test_chronological(kind, nodes):
                 assert np.array_equal(got.nbr, want.nbr)
                 assert np.array_equal(got.eid, want.eid)
                 assert np.array_equal(got.ts.view(np.int32), want.ts.view(np.int32))
+
+
+@pytest.mark.parametrize("m", [262_144, 262_145])
+def test_histogram_sizes(m):
+    """Digit histograms of 128 tiles of 4096 entries (16,384 counts, scanned by
+    one block) and of one tile more (the general scan)."""
+    require_gpu()
+    rng = np.random.default_rng(m)
+    src, dst = (rng.integers(0, 9000, m).astype(np.int32) for _ in range(2))
+    ts = np.sort(rng.random(m).astype(np.float32) * 1e6)
+    announce("edges %d" % m)
+    got = tcsr_to_host(P.tcsr_build(upload(src), upload(dst), upload(ts), None, 9000, True))
+    want = oracle.build_tcsr(src, dst, ts, None, 9000, True)
+    assert np.array_equal(got.indptr, want.indptr) and np.array_equal(got.eid, want.eid)
+    assert np.array_equal(got.nbr, want.nbr) and np.array_equal(got.ts, want.ts)
