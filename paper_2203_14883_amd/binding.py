@@ -163,8 +163,13 @@ def _p(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    # the current stream's handle without making a torch.cuda.Stream for it
+    # (0.4 us instead of 3 per call, a quarter of a small sampling call)
+    if torch.cuda.is_initialized():
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 def _i32_array(v: Sequence[int]):
