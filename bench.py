@@ -514,7 +514,7 @@ def measure_timeenc(args, w, smp, run, timed_pos, B, dev):
             "valid_fraction": nvalid / max(nslots, 1),
         },
         "roofline": {
-            "kernel": "timeenc_vec_kernel",
+            "kernel": "timeenc_word_kernel",
             "bound": "hbm",
             "achieved": achieved,
             "peak": PEAK_HBM_GBS,
