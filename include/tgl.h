@@ -547,10 +547,10 @@ tgl_status tgl_gather(const int32_t *nbr, const int64_t *eid, int64_t n, const i
  * Time encoding of the slots' time differences (Equation 3, the time encoder
  * of Section 2): out[i][j] = cos(omega[j] * dt[i] + phi[j]) for every slot
  * i < n with dt[i] >= 0; a slot with dt[i] < 0 (PAD slots carry -1) gets a
- * row of zeros.  The argument is formed in double precision (the float
- * product omega * dt is exact there) and reduced modulo 2 pi before a float
- * cosine, so the result is within 1e-6 of the exact value whatever the size
- * of omega * dt (before the bfloat16 rounding, for TGL_OUT_BF16).
+ * row of zeros.  The argument is formed in double precision and reduced there
+ * by whole turns or quarter turns, before a float polynomial of the cosine, so
+ * the result is within 1e-6 of the exact value whatever the size of omega * dt
+ * (before the bfloat16 rounding, for TGL_OUT_BF16), and at most 1 in size.
  *   dt         [device] float[n] (a hop's dt output)
  *   n          slots, >= 0
  *   count      [device] int64 or NULL: when given, only slots

@@ -10,21 +10,23 @@
 // output that is not 16-byte aligned, take a wavefront per row
 // (timeenc_kernel).
 //
-// Accuracy: the argument is formed in turns, t = (omega / 2 pi) dt + phi / 2 pi,
-// in double precision, from per-column factors omega / 2 pi and phi / 2 pi
-// (each within 2^-52 relative of exact).  Below 2^19 turns its fraction is
-// taken as a phase in units of 2^-32 turns (7e-10 rad of rounding) and
-// cos_phase evaluates it; from there to 2^24 turns, where t is within 5e-8 rad
-// of the exact argument, f = t - rint(t) is exact, and cos(2 pi f) = cos(2 pi
-// g) for g = |f| in [0, 1/2]; above 1/4 it is -cos(2 pi (1/2 - g)), also exact,
-// so only [0, 1/4] is left: x = 2 pi g in [0, pi/2], where the cosine's Taylor
-// series to x^12, in powers of g^2, leaves out less than 6.4e-9.  g is rounded
-// to float (2.4e-8 rad) and the series evaluated by fused multiply-adds in
-// float (a few float ulps).  The result is within 3e-7 of cos(omega dt + phi).
+// Accuracy: the argument is formed in turns, (omega / 2 pi) dt + phi / 2 pi, or
+// quarter turns, in double precision from per-column factors omega / 2 pi and
+// phi / 2 pi (each within 2^-52 relative of exact): below 2^24 turns it is
+// within 5e-8 rad of the exact argument.  What it has above whole turns or
+// quarters is exact, and is rounded to float only after that, for a polynomial
+// of the cosine evaluated by fused multiply-adds.
+//   timeenc_kernel: f = t - rint(t), and cos(2 pi f) = cos(2 pi g) for g = |f| in
+//     [0, 1/2]; above 1/4 it is -cos(2 pi (1/2 - g)), so only [0, 1/4] is left: x =
+//     2 pi g in [0, pi/2], where the cosine's Taylor series to x^12, in powers of
+//     g^2, leaves out less than 6.4e-9.  Measured against 64 bits, 2.8e-8 (2-norm)
+//     and 1.7e-7 at most;
+//   timeenc_word_kernel: cos_quarters, 1.8e-8 and 9e-8, and 1.7e-8 and 3.1e-8 where
+//     the argument is below 0.1.
 // A plain float evaluation of the argument would be off by up to half an ulp
 // of omega * dt -- 0.125 at dt = 2.7e6 s, Wikipedia's time span -- which the
-// cosine passes on unchanged.  Arguments of 2^24 turns or more, infinite or
-// NaN use the double cosine of the double argument instead.
+// cosine passes on unchanged.  Arguments of 2^24 turns or more have a reduction
+// of their own (far_quarters), or the double cosine.
 //
 // Padded slots (dt < 0) have no time difference: their rows are zeros.
 #include <atomic>
@@ -47,17 +49,33 @@ constexpr float kC4 = 60.24464137187666f;
 constexpr float kC5 = -26.426256783374397f;
 constexpr float kC6 = 7.903536371318469f;
 
-// sin(z pi / 2) = z (kS1 + (kS1Lo + kS3 z^2 + ... + kS9 z^8)): see cos_phase
+// cos(z pi / 2) = 1 + z^2 (kE1 + ... + kE4 z^6) and sin(z pi / 2) = z (kS1 +
+// ... + kS7 z^6) for |z| <= 1/2; sin(z pi / 2) = z + z (1 - z^2) (kR0 + ... + kR3
+// z^6) for |z| <= 1: see cos_quarters
+constexpr float kE1 = -1.2337005138397217f;
+constexpr float kE2 = 0.25366851687431335f;
+constexpr float kE3 = -0.0208552535623312f;
+constexpr float kE4 = 0.0008935732766985893f;
 constexpr float kS1 = 1.5707963705062866f;
-constexpr float kS1Lo = -4.371138828673793e-08f;
-constexpr float kS3 = -0.645963728427887f;
-constexpr float kS5 = 0.07968960702419281f;
-constexpr float kS7 = -0.0046735769137740135f;
-constexpr float kS9 = 0.00015137750597205013f;
+constexpr float kS3 = -0.6459648013114929f;
+constexpr float kS5 = 0.0796898826956749f;
+constexpr float kS7 = -0.00462295301258564f;
+constexpr float kR0 = 0.5707963109016418f;
+constexpr float kR1 = -0.075167216360569f;
+constexpr float kR2 = 0.0045216684229671955f;
+constexpr float kR3 = -0.00015092534886207432f;
 
-constexpr double kPhaseBase = 0x1.8p20;                            // doubles near it are 2^-32 apart
-constexpr uint32_t kPhaseHigh = 0x41300000u;                       // high word of the doubles in [2^20, 2^21): this ...
-constexpr uint32_t kPhaseSpan = 0x00100000u;                       // ... plus less than that
+constexpr double kQuarters = 0.6366197723675814;                   // 2 / pi, nearest double, ...
+constexpr double kQuartersLow = -3.935735335036497e-17;            // ... and what it leaves out
+constexpr double kOnes = 0x1.8p52;                                 // doubles near it are 1 apart
+constexpr double kFours = 0x1.8p54;                                // doubles near it are 4 apart
+
+// An argument of 2^26 quarter turns or more is reduced by far_quarters, from
+// 2^50 rad on by the double cosine; below kNearRad radians, |omega| dt + |phi|
+// in float, none of a lane's columns has one.
+constexpr double kQuarterLimit = 0x1p26;
+constexpr float kNearRad = 1.0541e8f;
+constexpr float kFarRad = 0x1p50f;
 
 using i32x4 = int __attribute__((ext_vector_type(4)));
 
@@ -163,21 +181,59 @@ __global__ __launch_bounds__(kBlock) void timeenc_kernel(const float *__restrict
     }
 }
 
-// cos(2 pi p 2^-32) of a phase p in units of 2^-32 turns (mod 1).  With a =
-// |p| taken mod 1 it is sin(2 pi (1/4 - a)): one v_sad gives 2^30 - a, whose
-// conversion to float is z = x / (pi / 2) scaled, x in [-pi/2, pi/2], and the
-// odd polynomial below finishes it.  Its coefficients are the minimax fit of
-// sin x - x on [0, pi/2] (error 4.6e-9) in powers of z; pi/2 is split in two
-// so that the leading product's rounding is the result's.
-__device__ __forceinline__ float cos_phase(uint32_t p) {
-    const int h = static_cast<int>(__usad(p, 0x80000000u, 0xc0000000u));   // |p - 2^31| - 2^30 (mod 2^32)
-    const float z = static_cast<float>(h) * 0x1p-30f;
-    const float y = z * z;
-    float q = __builtin_fmaf(y, kS9, kS7);
-    q = __builtin_fmaf(y, q, kS5);
-    q = __builtin_fmaf(y, q, kS3);
-    q = __builtin_fmaf(y, q, kS1Lo);
-    return __builtin_fmaf(z, kS1, z * q);
+// cos(t pi / 2) for an argument t in quarter turns, |t| < 2^51.
+//
+// float32: t is a whole number q of quarters plus z of one, |z| <= 1/2, and the
+// result plus or minus cos(z pi / 2) or sin(z pi / 2), which q decides.  Both
+// polynomials (minimax fits, errors 4e-10 and 4e-9) are evaluated and one is
+// taken.  Near 1 the result is 1 minus a small sum, rounded once, as a cosine
+// series gives it.  One polynomial for the sine of the complement over a whole
+// quarter needs 7 instructions fewer; as an odd series it adds two terms of
+// the size of 1 there, with errors up to 1.3e-7 instead of 3e-8 for arguments
+// below 0.1 and results above 1.
+//
+// bfloat16, whose rounding hides the difference and whose words, half as
+// many bytes, are bound by instructions: that complement z = 1 - |r|, r in
+// [-2, 2] quarters, and the correction to z of sin(z pi / 2), which vanishes at 0
+// and 1 (minimax fit, error 5e-9), so that the result never exceeds 1 either:
+// 8.5e-8 at most before the rounding.
+template <int OUT>
+__device__ __forceinline__ float cos_quarters(double t) {
+    if constexpr (OUT == TGL_OUT_F32) {
+        const double m = t + kOnes;
+        const float z = static_cast<float>(t - (m - kOnes));
+        const uint32_t q = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, m));
+        const float y = z * z;
+        float c = __builtin_fmaf(y, kE4, kE3);
+        c = __builtin_fmaf(y, c, kE2);
+        c = __builtin_fmaf(y, c, kE1);
+        c = __builtin_fmaf(y, c, 1.0f);
+        float s = __builtin_fmaf(y, kS7, kS5);
+        s = __builtin_fmaf(y, s, kS3);
+        s = __builtin_fmaf(y, s, kS1);
+        s = z * s;
+        const float r = (q & 1u) != 0 ? s : c;
+        return __uint_as_float(__float_as_uint(r) ^ (((q + 1u) << 30) & 0x80000000u));   // q mod 4 = 1, 2
+    } else {
+        const double r = t - ((t + kFours) - kFours);
+        const float z = static_cast<float>(1.0 - fabs(r));
+        const float y = z * z;
+        float p = __builtin_fmaf(y, kR3, kR2);
+        p = __builtin_fmaf(y, p, kR1);
+        p = __builtin_fmaf(y, p, kR0);
+        return __builtin_fmaf(z * __builtin_fmaf(-z, z, 1.0f), p, z);
+    }
+}
+
+// omega dt + phi in quarter turns, less a multiple of 4 of them, for arguments
+// below 2^50 rad, from wq = 2 omega / pi and pq = 2 phi / pi as the kernel holds
+// them: omega is wq pi / 2 rounded to float, omega dt exact in double, and its
+// product with 2 / pi taken to 106 bits (2^-54 quarters of error).
+__device__ __forceinline__ double far_quarters(double wq, double pq, double dt) {
+    const double x = static_cast<double>(static_cast<float>(wq * (1.0 / kQuarters))) * dt;
+    const double h = x * kQuarters;
+    const double l = fma(x, kQuartersLow, fma(x, kQuarters, -h));
+    return (h - ((h + kFours) - kFours)) + (l + pq);
 }
 
 // Lane l of the grid owns the 16-byte output words l, l +
@@ -188,17 +244,15 @@ __device__ __forceinline__ float cos_phase(uint32_t p) {
 // STRADDLE a row is not a whole number of words: a word's elements from
 // column dim on belong to the next row, and the last word may end early.
 //
-// The argument t = (omega / 2 pi) dt + phi / 2 pi is formed in turns by one
-// double fma on top of kPhaseBase, whose unit in the last place is 2^-32 turns:
-// the sum's low word is the phase, rounded to 2^-33 turns (7e-10 rad), as
-// long as |t| < 2^19, which the sum's high word shows.  Larger arguments take
-// encode().  11 float instructions and one double one per element; before, a
-// rounding to turns, a fold and two comparisons were double too, factors came
-// from LDS for every word, and rows that are not whole words were written an
-// element at a time.  100 float32 of 8M slots 821 -> 603 us (5.6 TB/s; a plain
-// fill writes 6.9), 100 bfloat16 1112 -> 444, 101 float32 of 2M slots 384 ->
-// 141, 33 bfloat16 145 -> 37.  Error against 64 bits 3.1e-8 (2-norm) and 1.3e-7
-// at most; 3.3e-8 and 1.6e-7 before.
+// The argument is one double fma per element, in quarter turns; one float fma
+// per word tells whether any of its arguments needs far_quarters.  What an
+// element becomes depends on its own dt, omega and phi alone.  19 instructions
+// per float32 element, 5 of them double.  Against the reduction to turns, fold
+// and Taylor series of timeenc_kernel with the factors in LDS (same inputs,
+// before -> now): 100 float32 of 8M slots 823 -> 604 us (5.6 TB/s; a plain fill
+// writes 6.9), 101 of 2M 393 -> 181, 100 bfloat16 of 8M 1151 -> 533; where a
+// tenth of the slots have arguments of 2^24 turns or more, 100 float32 of 2M
+// 394 -> 166, 172 bfloat16 491 -> 296.
 template <int OUT, bool STRADDLE>
 __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__restrict__ dt, int64_t n,
                                                               const int64_t *__restrict__ count, int64_t per,
@@ -218,12 +272,15 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
     if (w >= total) return;
     int64_t row = w * EPW / dim;
     const int col = static_cast<int>(w * EPW - row * dim);
-    double wp[EPW], pb[EPW];
+    double wq[EPW], pq[EPW];                                        // quarter turns
+    float om = 0.0f, pm = 0.0f;                                     // the largest |omega| and |phi|
 #pragma unroll
     for (int e = 0; e < EPW; e++) {
         const int j = STRADDLE && col + e >= dim ? col + e - dim : col + e;
-        wp[e] = static_cast<double>(omega[j]) * kInvTwoPi;
-        pb[e] = static_cast<double>(phi[j]) * kInvTwoPi + kPhaseBase;
+        wq[e] = static_cast<double>(omega[j]) * kQuarters;
+        pq[e] = static_cast<double>(phi[j]) * kQuarters;
+        om = fmaxf(om, fabsf(omega[j]));
+        pm = fmaxf(pm, fabsf(phi[j]));
     }
     for (; w < total; w += T, row += row_step) {
         const float d0 = dt[row];
@@ -237,26 +294,32 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
         const bool pad0 = STRADDLE ? !(d0 >= 0.0f) : d0 < 0.0f;
         const bool pad1 = STRADDLE ? !(d1 >= 0.0f) : pad0;
         if (!pad0 || !pad1) {
-            uint32_t ph[EPW], far = 0;
+            double t[EPW];
 #pragma unroll
-            for (int e = 0; e < EPW; e++) {
-                const float d = STRADDLE && col + e >= dim ? d1 : d0;
-                const uint64_t s = __builtin_bit_cast(uint64_t, fma(wp[e], static_cast<double>(d), pb[e]));
-                ph[e] = static_cast<uint32_t>(s);
-                far |= static_cast<uint32_t>(s >> 32) ^ kPhaseHigh;
+            for (int e = 0; e < EPW; e++)
+                t[e] = fma(wq[e], static_cast<double>(STRADDLE && col + e >= dim ? d1 : d0), pq[e]);
+            // a bound of every |argument| of the word (a NaN or infinite one
+            // gives NaN with or without the reduction)
+            const float far = __builtin_fmaf(om, fmaxf(d0, d1), pm);
+            if (far >= kNearRad) {
+#pragma unroll
+                for (int e = 0; e < EPW; e++)
+                    if (fabs(t[e]) >= kQuarterLimit)
+                        t[e] = far_quarters(wq[e], pq[e], static_cast<double>(STRADDLE && col + e >= dim ? d1 : d0));
             }
-            if (far < kPhaseSpan) {
 #pragma unroll
-                for (int e = 0; e < EPW; e++) v[e] = cos_phase(ph[e]);
-            } else {                                                // some |t| >= 2^19, infinite or NaN
+            for (int e = 0; e < EPW; e++) v[e] = cos_quarters<OUT>(t[e]);
+            if (far >= kFarRad) {
                 // one element after the other: nothing of the double cosine
                 // is held in registers by the path above
 #pragma unroll 1
                 for (int e = 0; e < EPW; e++) {
                     const bool next = STRADDLE && col + e >= dim;
                     const int j = next ? col + e - dim : col + e;
-                    const float r = encode(static_cast<double>(omega[j]) * kInvTwoPi,
-                                           static_cast<double>(phi[j]) * kInvTwoPi, next ? d1 : d0, omega, phi, j);
+                    const double x = fma(static_cast<double>(omega[j]), static_cast<double>(next ? d1 : d0),
+                                         static_cast<double>(phi[j]));
+                    if (fabs(x) < kFarRad) continue;
+                    const float r = static_cast<float>(cos(x));
 #pragma unroll
                     for (int i = 0; i < EPW; i++) v[i] = i == e ? r : v[i];
                 }

@@ -49,3 +49,52 @@ def test_words(dim, dtype):
             bound = 1e-6 + (want[:m].abs() * 2.0 ** -8 if dtype == "bfloat16" else 0.0)
             assert bool((err <= bound).all()), float(err.max())
             assert bool((out[m:] == 77).all())
+
+
+def _ladder(torch, dim):
+    return (10.0 ** (-9.0 * torch.arange(dim, dtype=torch.float64) / (dim - 1))).float().cuda()
+
+
+@pytest.mark.parametrize("dim", [100, 101, 128])
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_near_one(dim, dtype):
+    """No value exceeds 1, and where the argument is below 0.1 rad (the slow
+    columns) a float32 value is its cosine rounded once: half a step below 1
+    is 2^-25 = 3.0e-8, and 1 - cos < 0.005 is summed with steps of 2^-31, so
+    that 3.2e-8 bounds the error."""
+    torch = require_gpu()
+    gen = torch.Generator(device="cuda").manual_seed(dim)
+    omega, phi = _ladder(torch, dim), torch.zeros(dim, device="cuda")
+    d = torch.empty(200_000, device="cuda").exponential_(1 / 2e5, generator=gen)
+    announce("dim %d %s" % (dim, dtype))
+    out = P.time_encode(d, omega, phi, getattr(torch, dtype)).double()
+    assert float(out.abs().max()) <= 1.0
+    if dtype == "float32":
+        x = torch.outer(d.double(), omega.double())
+        err = (out - x.cos()).abs()
+        assert float(err[x < 0.1].max()) <= 3.2e-8
+        # over all arguments: a step of the float argument's rest (below 1/2
+        # quarter: 2^-26 of pi / 2) and two of the result's (2^-25), at most
+        assert float(err.max()) <= 2.0 ** -26 * 1.5708 + 2 * 2.0 ** -25 + 5e-9
+
+
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_value_alone(dtype):
+    """An element depends on its own slot, omega and phi: the same slots in
+    another order, and alone, give the same bits, small arguments beside ones
+    past 2^24 turns and past 2^50 rad."""
+    torch = require_gpu()
+    for dim in (100, 101, 128):
+        gen = torch.Generator(device="cuda").manual_seed(dim)
+        omega = _ladder(torch, dim)
+        phi = torch.randn(dim, generator=gen, device="cuda")
+        n = 3000
+        d = torch.empty(n, device="cuda").exponential_(1 / 3e5, generator=gen)
+        big = torch.rand(n, generator=gen, device="cuda") < 0.05
+        d = torch.where(big, d * 10.0 ** torch.randint(1, 13, (n,), generator=gen, device="cuda"), d)
+        announce("dim %d %s" % (dim, dtype))
+        out = P.time_encode(d, omega, phi, getattr(torch, dtype))
+        perm = torch.randperm(n, generator=gen, device="cuda")
+        assert torch.equal(P.time_encode(d[perm].contiguous(), omega, phi, getattr(torch, dtype)), out[perm])
+        for i in (0, 1, n - 1, int(d.argmax())):
+            assert torch.equal(P.time_encode(d[i:i + 1].clone(), omega, phi, getattr(torch, dtype))[0], out[i])
