@@ -236,6 +236,18 @@ __device__ __forceinline__ double far_quarters(double wq, double pq, double dt) 
     return (h - ((h + kFours) - kFours)) + (l + pq);
 }
 
+// Blocks that share `words` 16-byte words: one per `lane_words` words of its
+// lanes, at most `most`, and a multiple of `unit`; or a block per 256 words
+// when that is no more than `unit` (one word per lane: no step is taken).
+__host__ __device__ __forceinline__ uint32_t word_blocks(int64_t words, int lane_words, uint32_t most, uint32_t unit) {
+    const int64_t whole = words / kBlock + (words % kBlock != 0);
+    const int64_t even = whole / lane_words + (whole % lane_words != 0);
+    uint32_t nb = even < most ? static_cast<uint32_t>(even) : most;
+    nb = nb / unit * unit;
+    nb = nb < unit ? unit : nb;
+    return whole < nb ? static_cast<uint32_t>(whole) : nb;
+}
+
 // Lane l of the grid owns the 16-byte output words l, l +
 // T, ... (EPW elements each: 4 float32 or 8 bfloat16; T lanes in all), so one
 // store instruction writes 1 KB of contiguous output.  T * EPW is a multiple
@@ -249,16 +261,17 @@ __device__ __forceinline__ double far_quarters(double wq, double pq, double dt) 
 // element becomes depends on its own dt, omega and phi alone.  19 instructions
 // per float32 element, 5 of them double.  Against the reduction to turns, fold
 // and Taylor series of timeenc_kernel with the factors in LDS (same inputs,
-// before -> now): 100 float32 of 8M slots 823 -> 604 us (5.6 TB/s; a plain fill
-// writes 6.9), 101 of 2M 393 -> 181, 100 bfloat16 of 8M 1151 -> 533; where a
-// tenth of the slots have arguments of 2^24 turns or more, 100 float32 of 2M
-// 394 -> 166, 172 bfloat16 491 -> 296.
+// before -> now): 100 float32 of 8M slots 829 -> 584 us (5.8 TB/s; a plain fill
+// writes 6.9), 101 of 2M 395 -> 191, 100 bfloat16 of 8M 1156 -> 509; where a
+// third of the slots have arguments of 2^24 turns or more, 100 float32 of 2M
+// 397 -> 174, 172 bfloat16 496 -> 259.
 template <int OUT, bool STRADDLE>
 __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__restrict__ dt, int64_t n,
                                                               const int64_t *__restrict__ count, int64_t per,
                                                               const float *__restrict__ omega,
                                                               const float *__restrict__ phi, int dim,
-                                                              int64_t row_step, void *__restrict__ out) {
+                                                              int lane_words, uint32_t most, uint32_t unit,
+                                                              void *__restrict__ out) {
     constexpr int EPW = OUT == TGL_OUT_F32 ? 4 : 8;                 // elements per 16-byte word
     if (count) {
         const int64_t c = *count;
@@ -267,7 +280,12 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
     }
     const int64_t elems = n * dim;
     const int64_t total = (elems + EPW - 1) / EPW;                  // words
-    const int64_t T = static_cast<int64_t>(gridDim.x) * kBlock;
+    // the blocks that the slots counted on the device need: the grid is for
+    // all n, and with few of them valid its other blocks end here
+    const uint32_t nb = word_blocks(total, lane_words, most, unit);
+    if (blockIdx.x >= nb) return;
+    const int64_t T = static_cast<int64_t>(nb) * kBlock;
+    const int64_t row_step = T * EPW / dim;
     int64_t w = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (w >= total) return;
     int64_t row = w * EPW / dim;
@@ -349,11 +367,11 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
     }
 }
 
-// Both kernels stride over their work, so a grid of the blocks the device
-// holds at once does all of it and loads each block's or lane's factors once.
-// Found once per device and kernel (CUs x resident blocks per CU).
+// timeenc_kernel strides over its rows, so a grid of the blocks the device
+// holds at once does all of them and loads each block's factors once.  Found
+// once per device and kernel (CUs x resident blocks per CU).
 constexpr int kMaxDevices = 64;
-constexpr int kVariants = 8;                                       // row/word kernel x output x factor table or straddle
+constexpr int kVariants = 4;                                       // output x factor table
 std::atomic<int> g_resident[kMaxDevices][kVariants];
 
 template <typename K>
@@ -380,33 +398,28 @@ unsigned resident_grid(K kernel, int variant, int64_t want) {
 int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
 
 // Words per lane, which make its setup (a division, its columns' factors)
-// small.  100 float32 of 8M slots take 633 us on the blocks resident together,
-// 603 on a block per 8 words of its lanes, 590 per 32 and 641 per 128; 172 of 2M
-// slots 272, 229, 256 and 281.  100 bfloat16 of 8M slots 444, 507, 425 and 425,
-// and 128 of 2M slots 117, 170, 147 and 119: float32 takes blocks of 8 words,
-// bfloat16 the resident ones.
-constexpr int64_t kLaneWordsF32 = 8;
-constexpr int64_t kLaneWordsBf16 = 4;
-constexpr int64_t kMaxBlocks = 1 << 22;
+// small: 100 float32 of 600,000 slots 57 us with 2, 55 with 4, 48 with 8; of
+// 18,000 slots 6 with 8, 9 with 16.  And blocks at most, so that a call for many
+// slots of which the device counts few does not wait for empty blocks (20M
+// slots, 2,000 of them valid: 6, 8 and 15 us on 4096, 8192 and 16384 blocks, 100
+// on as many as there are words for), with the full calls' times, on 4096 / 8192 /
+// 16384 / 25600 blocks: 100 float32 of 8M slots 685 / 591 / 584 / 591 us, 172 of
+// 2M 280 / 281 / 258 / 265, 128 of 2M 268 / 220 / 195 / 206; 100 bfloat16 of 8M
+// 510 / 508 / 520 / 535, 128 of 2M 139 / 148 / 187 / 245 (6144: 137).
+constexpr int kLaneWordsF32 = 8;
+constexpr int kLaneWordsBf16 = 4;
+constexpr uint32_t kMostF32 = 16384;
+constexpr uint32_t kMostBf16 = 6144;
 
-// timeenc_word_kernel on a multiple of `unit` blocks, or on a block per 256
-// words when that is no more than `unit`.
 template <typename K>
-void launch_words(K kernel, int variant, int epw, int unit, hipStream_t st, const float *dt, int64_t n,
-                  const int64_t *count, int64_t per, const float *omega, const float *phi, int dim, void *out) {
+void launch_words(K kernel, int epw, int unit, hipStream_t st, const float *dt, int64_t n, const int64_t *count,
+                  int64_t per, const float *omega, const float *phi, int dim, void *out) {
     const int64_t words = n > INT64_MAX / dim - epw ? INT64_MAX / epw : (n * dim + epw - 1) / epw;
-    const int64_t whole = words / kBlock + (words % kBlock != 0);
-    const bool f32 = epw == 4;
-    const int64_t lane_words = f32 ? kLaneWordsF32 : kLaneWordsBf16;
-    const int64_t most = f32 ? kMaxBlocks : resident_grid(kernel, variant, kMaxBlocks);
-    int64_t nb = whole / lane_words + (whole % lane_words != 0);
-    if (nb > most) nb = most;
-    nb = nb / unit * unit;
-    if (nb < unit) nb = unit;
-    if (nb > whole) nb = whole;                                    // one word per lane: no step is taken
-    const int64_t row_step = nb * kBlock * epw / dim;
+    const int lane_words = epw == 4 ? kLaneWordsF32 : kLaneWordsBf16;
+    const uint32_t most = epw == 4 ? kMostF32 : kMostBf16;
     ScopedTimer tm(TGL_TIMER_TIMEENC, st);
-    kernel<<<static_cast<unsigned>(nb), kBlock, 0, st>>>(dt, n, count, per, omega, phi, dim, row_step, out);
+    kernel<<<word_blocks(words, lane_words, most, static_cast<uint32_t>(unit)), kBlock, 0, st>>>(
+        dt, n, count, per, omega, phi, dim, lane_words, most, static_cast<uint32_t>(unit), out);
 }
 
 template <typename K>
@@ -445,13 +458,13 @@ tgl_status tgl_time_encode(const float *dt, int64_t n, const int64_t *count, int
     if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0 && dim >= epw) {
         const bool straddle = dim % epw != 0;
         if (out_type == TGL_OUT_F32 && straddle)
-            launch_words(timeenc_word_kernel<TGL_OUT_F32, true>, 5, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+            launch_words(timeenc_word_kernel<TGL_OUT_F32, true>, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
         else if (out_type == TGL_OUT_F32)
-            launch_words(timeenc_word_kernel<TGL_OUT_F32, false>, 4, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+            launch_words(timeenc_word_kernel<TGL_OUT_F32, false>, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
         else if (straddle)
-            launch_words(timeenc_word_kernel<TGL_OUT_BF16, true>, 7, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+            launch_words(timeenc_word_kernel<TGL_OUT_BF16, true>, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
         else
-            launch_words(timeenc_word_kernel<TGL_OUT_BF16, false>, 6, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
+            launch_words(timeenc_word_kernel<TGL_OUT_BF16, false>, epw, unit, st, dt, n, count, per_count, omega, phi, dim, out);
         return launch_status();
     }
     constexpr int64_t rows_per_block = static_cast<int64_t>(kBlock / kWave) * kRows;

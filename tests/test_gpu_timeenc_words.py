@@ -98,3 +98,25 @@ def test_value_alone(dtype):
         assert torch.equal(P.time_encode(d[perm].contiguous(), omega, phi, getattr(torch, dtype)), out[perm])
         for i in (0, 1, n - 1, int(d.argmax())):
             assert torch.equal(P.time_encode(d[i:i + 1].clone(), omega, phi, getattr(torch, dtype))[0], out[i])
+
+
+@pytest.mark.parametrize("dim", [33, 100, 128, 172])
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_few_counted(dim, dtype):
+    """Calls for many slots of which the device counts few: as many blocks as
+    the counted slots need take part, from one to the most there are, and
+    the counted rows hold the bits of a call for those slots alone."""
+    torch = require_gpu()
+    dt_ = getattr(torch, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(dim)
+    omega, phi = _ladder(torch, dim), torch.randn(dim, generator=gen, device="cuda")
+    n = 1_500_000
+    d = torch.empty(n, device="cuda").exponential_(1 / 3e5, generator=gen)
+    out = torch.empty(n, dim, dtype=dt_, device="cuda")
+    for cnt in (0, 1, 2, 31, 4096, 4097, 50_003, 333_333, 1_499_999, n):
+        announce("dim %d %s count %d" % (dim, dtype, cnt))
+        out.fill_(77)
+        P.time_encode(d, omega, phi, dt_, count=torch.tensor([cnt], device="cuda"), out=out)
+        if cnt:
+            assert torch.equal(out[:cnt], P.time_encode(d[:cnt].clone(), omega, phi, dt_))
+        assert bool((out[cnt:] == 77).all())
