@@ -236,6 +236,10 @@ __device__ __forceinline__ double far_quarters(double wq, double pq, double dt) 
     return (h - ((h + kFours) - kFours)) + (l + pq);
 }
 
+// Words of a lane whose time differences are loaded ahead: with dt in memory
+// 100 float32 of 8M slots take 818, 717 and 596 us with 1, 2 and 4.
+constexpr int kAhead = 4;
+
 // Blocks that share `words` 16-byte words: one per `lane_words` words of its
 // lanes, at most `most`, and a multiple of `unit`; or a block per 256 words
 // when that is no more than `unit` (one word per lane: no step is taken).
@@ -256,15 +260,22 @@ __host__ __device__ __forceinline__ uint32_t word_blocks(int64_t words, int lane
 // STRADDLE a row is not a whole number of words: a word's elements from
 // column dim on belong to the next row, and the last word may end early.
 //
+// A lane loads the time differences of kAhead words before it encodes and
+// stores the kAhead before them.  Loads and stores complete in order, so that a
+// load after a store waits for it too, and with a load per word that is what a
+// word took where dt came from memory (a step's 8M slots, half of them PAD, 100
+// float32: 856 -> 593 us; dt in the cache 566 -> 592).
+//
 // The argument is one double fma per element, in quarter turns; one float fma
 // per word tells whether any of its arguments needs far_quarters.  What an
 // element becomes depends on its own dt, omega and phi alone.  19 instructions
 // per float32 element, 5 of them double.  Against the reduction to turns, fold
 // and Taylor series of timeenc_kernel with the factors in LDS (same inputs,
-// before -> now): 100 float32 of 8M slots 829 -> 584 us (5.8 TB/s; a plain fill
-// writes 6.9), 101 of 2M 395 -> 191, 100 bfloat16 of 8M 1156 -> 509; where a
+// before -> now): 100 float32 of 8M slots 691 -> 593 us with dt in memory (5.7
+// TB/s; a plain fill writes 6.9) and 827 -> 605 with dt in the cache and no PAD,
+// 101 of 2M 396 -> 204, 100 bfloat16 of 8M 1025 -> 470 and 1156 -> 520; where a
 // third of the slots have arguments of 2^24 turns or more, 100 float32 of 2M
-// 397 -> 174, 172 bfloat16 496 -> 259.
+// 395 -> 186, 172 bfloat16 498 -> 285.
 template <int OUT, bool STRADDLE>
 __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__restrict__ dt, int64_t n,
                                                               const int64_t *__restrict__ count, int64_t per,
@@ -300,70 +311,98 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
         om = fmaxf(om, fabsf(omega[j]));
         pm = fmaxf(pm, fabsf(phi[j]));
     }
-    for (; w < total; w += T, row += row_step) {
-        const float d0 = dt[row];
-        float d1 = d0;
-        if constexpr (STRADDLE) d1 = dt[row + 1 < n ? row + 1 : row];
-        float v[EPW];
+    // time differences of the lane's next kAhead words (STRADDLE: and of the rows
+    // after theirs); past its last word, of a row that is there
+    struct Ahead {
+        float d0[kAhead], d1[kAhead];
+    };
+    const auto load_ahead = [&](int64_t w0, int64_t r0) {
+        Ahead a;
 #pragma unroll
-        for (int e = 0; e < EPW; e++) v[e] = 0.0f;
-        // PAD slots; a NaN time difference gives NaN, or zeros in rows that
-        // are not whole words
-        const bool pad0 = STRADDLE ? !(d0 >= 0.0f) : d0 < 0.0f;
-        const bool pad1 = STRADDLE ? !(d1 >= 0.0f) : pad0;
-        if (!pad0 || !pad1) {
-            double t[EPW];
+        for (int u = 0; u < kAhead; u++) {
+            const int64_t r = w0 + u * T < total ? r0 + u * row_step : row;
+            a.d0[u] = dt[r];
+            a.d1[u] = STRADDLE ? dt[r + 1 < n ? r + 1 : r] : a.d0[u];
+        }
+        return a;
+    };
+    Ahead now = load_ahead(w, row);
+    // in registers here, so that the loop holds no wait for them
 #pragma unroll
-            for (int e = 0; e < EPW; e++)
-                t[e] = fma(wq[e], static_cast<double>(STRADDLE && col + e >= dim ? d1 : d0), pq[e]);
-            // a bound of every |argument| of the word (a NaN or infinite one
-            // gives NaN with or without the reduction)
-            const float far = __builtin_fmaf(om, fmaxf(d0, d1), pm);
-            if (far >= kNearRad) {
+    for (int u = 0; u < kAhead; u++) asm volatile("" : "+v"(now.d0[u]), "+v"(now.d1[u]));
+    for (;;) {
+        const Ahead next = load_ahead(w + kAhead * T, row + kAhead * row_step);
+#pragma unroll 1
+        for (int u = 0; u < kAhead && w < total; u++, w += T, row += row_step) {
+            const float d0 = now.d0[0], d1 = now.d1[0];
+#pragma unroll
+            for (int i = 0; i + 1 < kAhead; i++) {
+                now.d0[i] = now.d0[i + 1];
+                now.d1[i] = now.d1[i + 1];
+            }
+            float v[EPW];
+#pragma unroll
+            for (int e = 0; e < EPW; e++) v[e] = 0.0f;
+            // PAD slots; a NaN time difference gives NaN, or zeros in rows that
+            // are not whole words
+            const bool pad0 = STRADDLE ? !(d0 >= 0.0f) : d0 < 0.0f;
+            const bool pad1 = STRADDLE ? !(d1 >= 0.0f) : pad0;
+            if (!pad0 || !pad1) {
+                double t[EPW];
 #pragma unroll
                 for (int e = 0; e < EPW; e++)
-                    if (fabs(t[e]) >= kQuarterLimit)
-                        t[e] = far_quarters(wq[e], pq[e], static_cast<double>(STRADDLE && col + e >= dim ? d1 : d0));
-            }
+                    t[e] = fma(wq[e], static_cast<double>(STRADDLE && col + e >= dim ? d1 : d0), pq[e]);
+                // a bound of every |argument| of the word (a NaN or infinite one
+                // gives NaN with or without the reduction)
+                const float far = __builtin_fmaf(om, fmaxf(d0, d1), pm);
+                if (far >= kNearRad) {
 #pragma unroll
-            for (int e = 0; e < EPW; e++) v[e] = cos_quarters<OUT>(t[e]);
-            if (far >= kFarRad) {
-                // one element after the other: nothing of the double cosine
-                // is held in registers by the path above
+                    for (int e = 0; e < EPW; e++)
+                        if (fabs(t[e]) >= kQuarterLimit)
+                            t[e] = far_quarters(wq[e], pq[e], static_cast<double>(STRADDLE && col + e >= dim ? d1 : d0));
+                }
+#pragma unroll
+                for (int e = 0; e < EPW; e++) v[e] = cos_quarters<OUT>(t[e]);
+                if (far >= kFarRad) {
+                    // one element after the other: nothing of the double cosine
+                    // is held in registers by the path above
 #pragma unroll 1
-                for (int e = 0; e < EPW; e++) {
-                    const bool next = STRADDLE && col + e >= dim;
-                    const int j = next ? col + e - dim : col + e;
-                    const double x = fma(static_cast<double>(omega[j]), static_cast<double>(next ? d1 : d0),
-                                         static_cast<double>(phi[j]));
-                    if (fabs(x) < kFarRad) continue;
-                    const float r = static_cast<float>(cos(x));
+                    for (int e = 0; e < EPW; e++) {
+                        const bool next = STRADDLE && col + e >= dim;
+                        const int j = next ? col + e - dim : col + e;
+                        const double x = fma(static_cast<double>(omega[j]), static_cast<double>(next ? d1 : d0),
+                                             static_cast<double>(phi[j]));
+                        if (fabs(x) < kFarRad) continue;
+                        const float r = static_cast<float>(cos(x));
 #pragma unroll
-                    for (int i = 0; i < EPW; i++) v[i] = i == e ? r : v[i];
+                        for (int i = 0; i < EPW; i++) v[i] = i == e ? r : v[i];
+                    }
+                }
+                if constexpr (STRADDLE) {
+#pragma unroll
+                    for (int e = 0; e < EPW; e++)
+                        if (col + e >= dim ? pad1 : pad0) v[e] = 0.0f;
                 }
             }
-            if constexpr (STRADDLE) {
+            if (STRADDLE && w * EPW + EPW > elems) {                    // the last word, cut short
 #pragma unroll
-                for (int e = 0; e < EPW; e++)
-                    if (col + e >= dim ? pad1 : pad0) v[e] = 0.0f;
-            }
-        }
-        if (STRADDLE && w * EPW + EPW > elems) {                    // the last word, cut short
-#pragma unroll
-            for (int e = 0; e < EPW; e++) {
-                if (w * EPW + e >= elems) continue;
-                if constexpr (OUT == TGL_OUT_F32) static_cast<float *>(out)[w * EPW + e] = v[e];
-                else static_cast<uint16_t *>(out)[w * EPW + e] = to_bf16(v[e]);
-            }
-        } else {
-            i32x4 word;
-            if constexpr (OUT == TGL_OUT_F32) {
-                word = i32x4{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])};
+                for (int e = 0; e < EPW; e++) {
+                    if (w * EPW + e >= elems) continue;
+                    if constexpr (OUT == TGL_OUT_F32) static_cast<float *>(out)[w * EPW + e] = v[e];
+                    else static_cast<uint16_t *>(out)[w * EPW + e] = to_bf16(v[e]);
+                }
             } else {
-                word = i32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+                i32x4 word;
+                if constexpr (OUT == TGL_OUT_F32) {
+                    word = i32x4{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])};
+                } else {
+                    word = i32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+                }
+                __builtin_nontemporal_store(word, static_cast<i32x4 *>(out) + w);
             }
-            __builtin_nontemporal_store(word, static_cast<i32x4 *>(out) + w);
         }
+        if (w >= total) break;
+        now = next;
     }
 }
 
@@ -398,14 +437,15 @@ unsigned resident_grid(K kernel, int variant, int64_t want) {
 int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
 
 // Words per lane, which make its setup (a division, its columns' factors)
-// small: 100 float32 of 600,000 slots 57 us with 2, 55 with 4, 48 with 8; of
-// 18,000 slots 6 with 8, 9 with 16.  And blocks at most, so that a call for many
-// slots of which the device counts few does not wait for empty blocks (20M
-// slots, 2,000 of them valid: 6, 8 and 15 us on 4096, 8192 and 16384 blocks, 100
-// on as many as there are words for), with the full calls' times, on 4096 / 8192 /
-// 16384 / 25600 blocks: 100 float32 of 8M slots 685 / 591 / 584 / 591 us, 172 of
-// 2M 280 / 281 / 258 / 265, 128 of 2M 268 / 220 / 195 / 206; 100 bfloat16 of 8M
-// 510 / 508 / 520 / 535, 128 of 2M 139 / 148 / 187 / 245 (6144: 137).
+// small: 100 float32 of 600,000 slots take 60 us with 4 and 51 with 8; of 18,000
+// slots 6 with 8 and 9 with 16.  And blocks at most, so that a call for many slots
+// of which the device counts few does not wait for empty blocks (20M slots, 2,000
+// of them valid: 6, 9 and 16 us on 4096, 8192 and 16384 blocks, 100 on as many as
+// there are words for).  Full calls on 4096 / 8192 / 16384 / 25600 blocks: 100
+// float32 of 8M slots 636 / 603 / 605 / 614 us, 172 of 2M 260 / 261 / 269 / 279,
+// 128 of 2M 264 / 240 / 203 / 214; bfloat16 on 4096 / 6144 / 8192 / 25600: 100 of
+// 8M 516 / 519 / 523 / 556, 128 of 2M 135 / 140 / 148 / 253, 100 of 64M 4219 / 4139
+// / 4116 / 4089.
 constexpr int kLaneWordsF32 = 8;
 constexpr int kLaneWordsBf16 = 4;
 constexpr uint32_t kMostF32 = 16384;
