@@ -47,6 +47,7 @@ struct GatherArgs {
     int64_t n;
     const int64_t *count;  // or null
     int64_t per;
+    int64_t whole;         // n / per
     GatherTable t[TGL_MAX_TABLES];
 };
 
@@ -61,13 +62,14 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const GatherArgs a) {
     if (a.count) {
         // valid prefix: min(n, count * per), without overflowing the product
         const int64_t c = *a.count;
-        const int64_t lim = c <= 0 ? 0 : (c > n / a.per ? n : c * a.per);
+        const int64_t lim = c <= 0 ? 0 : (c > a.whole ? n : c * a.per);
         n = lim < n ? lim : n;
     }
     const i32x4 zero = {0, 0, 0, 0};
     const uint32_t W = static_cast<uint32_t>(T.words);
     const int64_t total = n * W;
     const int64_t step = waves * kSpan;
+    if (wave * kSpan >= total) return;
     // the span's first word as (row0, off0), advanced without dividing
     const int64_t step_q = step / W;
     const uint32_t step_r = static_cast<uint32_t>(step - step_q * W);
@@ -118,6 +120,7 @@ tgl_status tgl_gather(const int32_t *nbr, const int64_t *eid, int64_t n, const i
     a.n = n;
     a.count = count;
     a.per = per_count;
+    a.whole = n / per_count;
     int64_t most = 0;                           // words of the widest row
     for (int i = 0; i < num_tables; i++) {
         const tgl_table &t = tables[i];
@@ -145,9 +148,14 @@ tgl_status tgl_gather(const int32_t *nbr, const int64_t *eid, int64_t n, const i
     constexpr int64_t kPerBlock = static_cast<int64_t>(kBlock) * kFlat;      // words
     // blocks for the widest table, n * most words (without overflow), capped
     // (fewer, longer blocks are slower: 4M slots of 768 bf16 1.79 / 1.74 / 1.66 /
-    // 1.58 ms on 4 Ki, 16 Ki, 64 Ki and a block per 16 KB)
-    constexpr int64_t kMaxBlocks = 1 << 22;
-    int64_t blocks = n > kMaxBlocks * kPerBlock / most ? kMaxBlocks : (n * most + kPerBlock - 1) / kPerBlock;
+    // 1.58 ms on 4 Ki, 16 Ki, 64 Ki and a block per 16 KB).  With a count, which
+    // may be far below n, a call for a hop's capacity would wait for blocks with
+    // nothing to do: 5.2M slots of three tables, 2,000 of them counted, 303 us on
+    // a block per 16 KB, 23 on 96 Ki in all, 12 on 48 Ki and below; all counted 3480,
+    // 3437 and 3458 us (3490 on 12 Ki).
+    constexpr int64_t kCountedBlocks = 48 << 10;
+    const int64_t max_blocks = count ? kCountedBlocks / num_tables : 1 << 22;
+    int64_t blocks = n > max_blocks * kPerBlock / most ? max_blocks : (n * most + kPerBlock - 1) / kPerBlock;
     {
         ScopedTimer tm(TGL_TIMER_GATHER, st);
         gather_kernel<<<dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(num_tables)), kBlock, 0, st>>>(a);

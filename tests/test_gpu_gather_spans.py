@@ -37,3 +37,28 @@ def test_spans(words):
                 ok = (k >= 0) & (k < t.shape[0])
                 want = torch.where(ok[:, None], t[k.clamp(0, t.shape[0] - 1)], 0)
                 assert torch.equal(o[:m], want) and bool((o[m:] == 77).all())
+
+
+def test_counted_blocks():
+    """A call with a count runs on a bounded number of blocks (6144 for eight
+    tables, of 1024 words a round): one word more than they cover in a round, and
+    counts from none to all."""
+    torch = require_gpu()
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    words, rows, n = 64, 1000, 6144 * 1024 // 64 + 1
+
+    def table(w):
+        return torch.randint(-2**31, 2**31 - 1, (rows, 4 * w), generator=gen, device="cuda", dtype=torch.int32)
+
+    nbr = torch.randint(-3, rows + 3, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    eid = torch.randint(-3, rows + 3, (n,), generator=gen, device="cuda")
+    tabs = [(table(words), "node"), (table(words), "edge")] + [(table(1 + i), "node") for i in range(6)]
+    for cnt in (0, 1, 17, n // 2, n - 1, n, n + 5):
+        announce("count %d of %d" % (cnt, n))
+        outs = [torch.full((n, t.shape[1]), 77, dtype=torch.int32, device="cuda") for t, _ in tabs]
+        P.gather(nbr, eid, tabs, count=torch.tensor([cnt], device="cuda"), outs=outs)
+        m = min(n, cnt)
+        for (t, key), o in zip(tabs, outs):
+            k = (nbr if key == "node" else eid).long()[:m]
+            want = torch.where(((k >= 0) & (k < rows))[:, None], t[k.clamp(0, rows - 1)], 0)
+            assert torch.equal(o[:m], want) and bool((o[m:] == 77).all())
