@@ -320,11 +320,29 @@ using i32x4 = int __attribute__((ext_vector_type(4), aligned(4)));
 
 // Most groups whose counts are left unscanned: every wavefront of the next
 // hop then sums the counts before its chunk itself, 16 bytes per lane and
-// load (slots_before).  The two scan kernels take 9 us with their launches
-// whatever the size of a small call; summing instead costs the next hop
-// nothing at 1,800 groups (10.0 -> 9.5 us, 18,000 candidates) and 1.6 us at
-// 6,000 (10.0 -> 11.6 us, 60,000 candidates), growing with the groups.
+// load (slots_before).  The two scan kernels take 4 us between the hops of a
+// call of any size; summing instead costs the next hop nothing at 1,800 groups
+// (10.0 -> 9.5 us, 18,000 candidates) and 1.6 us at 6,000 (10.0 -> 11.6 us, 60,000
+// candidates).  It grows with the groups and with the wavefronts that sum, so
+// there are limits on both (unscanned_ok).
 constexpr int64_t kUnscannedGroups = 8192;
+
+// Whether the counts of at most `groups` groups, with `slots` slots, the next
+// hop's candidates, are left unscanned.  Two-hop calls of `groups` roots with
+// fanouts (k, 2), summed / scanned (us):
+//   hops with histories, bound by the records they gather: 1024 x 1024 slots 151 /
+//   155, 4096 x 100 42 / 46, 4096 x 1024 284 / 286, 8192 x 20 23 / 26, 8192 x 200 118 /
+//   120, 8192 x 1024 550 / 527, where 131,072 wavefronts read 2 GB of counts.  The
+//   line is at 2^34 of groups x slots;
+//   hops that search, whose scanned kernel runs 6 or 7 wavefronts per SIMD instead
+//   of 4: 512 x 1024 114 / 118, 2048 x 100 41 / 46, 4096 x 50 40 / 44, 8192 x 20 31 / 34,
+//   and with the chip full of wavefronts 2048 x 200 67 / 63, 4096 x 100 63 / 60, 8192 x
+//   50 63 / 58, 8192 x 1024 727 / 691.  The line is at 2^18 slots, with 512 groups or
+//   fewer there is none.
+bool unscanned_ok(int64_t groups, int64_t slots, bool histories) {
+    if (groups > kUnscannedGroups) return false;
+    return histories ? slots <= (int64_t(1) << 34) / (groups > 0 ? groups : 1) : groups <= 512 || slots <= int64_t(1) << 18;
+}
 
 // Valid slots before slot v0, a wavefront-uniform value, from the groups' raw
 // counts (k slots per group, the valid ones a prefix): the counts of the
@@ -1477,7 +1495,7 @@ tgl_status tgl_sample_ex(const tgl_tcsr *g, const int32_t *roots, const float *r
 
         // ---- exclusive scan of this hop's group counts -> next hop's indices ----
         const int64_t groups_cap = h == 1 ? num_roots * S : cap[h - 1];
-        scanned = groups_cap > kUnscannedGroups;
+        scanned = !unscanned_ok(groups_cap, cap[h], win);
         if (!scanned) continue;
         const int64_t *groups_dyn = h == 1 ? nullptr : counts + (h - 1);
         const int64_t tiles = scan_tiles(groups_cap) > 0 ? scan_tiles(groups_cap) : 1;

@@ -2,7 +2,8 @@
 the oracle bit for bit: chunks of 8, 16, 32 and 64 candidates per wavefront
 (one root, around a chunk, around the numbers of roots where the chunk
 doubles), and the hops that take their root indices from raw counts (at most
-8192 groups) or from a scan, on both sides of that line."""
+8192 groups, with limits on their slots) or from a scan, on both sides of those
+lines."""
 import math
 
 import numpy as np
@@ -53,3 +54,20 @@ def test_sizes(graphs, n, fan, mode, S, anchor, hist):
     want = oracle.sample(og, x, t, fan, mode, S, delta, seed=5, root_base=17, anchor=anchor)
     assert [h["num_roots"] for h in got] == [h.num_roots for h in want]
     assert_hops_equal(got, want, "roots %d" % n)
+
+
+# where the counts of few groups are scanned after all: past 512 groups and 2^18
+# slots of a hop whose next one searches, past 2^34 of groups x slots with histories
+@pytest.mark.parametrize("n,fan,hist", [(4096, (64, 2), False), (4096, (65, 2), False), (4097, (64, 2), False),
+                                        (512, (520, 1), False), (513, (520, 1), False), (8192, (256, 1), True),
+                                        (8192, (257, 1), True), (4096, (1024, 1), True), (64, (64, 64, 1), False),
+                                        (64, (64, 65, 1), False)])
+def test_wide_fanouts(graphs, n, fan, hist):
+    w, og, gs = graphs
+    x, t = _roots(w, n)
+    for mode in ("uniform", "recent"):
+        announce("roots %d fan %s %s hist=%s" % (n, fan, mode, hist))
+        got = hops_to_numpy(P.sample(gs[hist], upload(x, np.int32), upload(t, np.float32), fan, mode, 1, math.inf, 5, 17))
+        want = oracle.sample(og, x, t, fan, mode, 1, math.inf, seed=5, root_base=17)
+        assert [h["num_roots"] for h in got] == [h.num_roots for h in want]
+        assert_hops_equal(got, want, "roots %d fan %s" % (n, fan))
