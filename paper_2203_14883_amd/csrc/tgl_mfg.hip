@@ -242,7 +242,11 @@ MfgWs carve_mfg_ws(void *base, int64_t groups_cap) {
     const int tile = tile_groups(groups_cap);
     w.tiles = groups_cap > 0 ? (groups_cap + tile - 1) / tile : 1;
     w.packed = cv.take<uint32_t>(static_cast<size_t>(groups_cap > 0 ? groups_cap : 1));
-    w.partials = cv.take<int64_t>(static_cast<size_t>(w.tiles + 1));
+    // a capacity above kSmallGroups has fewer tiles than that one; room for as
+    // many, so that a workspace for some capacity serves every smaller one
+    const int64_t small_tiles = kSmallGroups / kTileLeast;
+    w.partials = cv.take<int64_t>(static_cast<size_t>(
+        (groups_cap > kSmallGroups && w.tiles < small_tiles ? small_tiles : w.tiles) + 1));
     w.bytes = cv.size();
     return w;
 }

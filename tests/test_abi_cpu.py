@@ -322,3 +322,17 @@ def test_column_view_binding_checks_its_arguments():
         a.update(bad)
         with pytest.raises(ValueError):
             P.tcsr_from_columns(a["indptr"], a["nbr"], a["ts"], a["eid"])
+
+
+def test_workspaces_grow_with_the_call():
+    """A workspace sized for the largest call serves every smaller one: the
+    sizes never fall as the capacity grows, over the powers of two (where launch
+    rules change) and between."""
+    L = P.lib()
+    edges = sorted({max(0, (1 << b) + d) for b in range(24) for d in (-300, -2, -1, 0, 1, 2, 300)}
+                   | {(1 << 20) + 1024 * i for i in range(8)} | {3 << b for b in range(22)})
+    fan = (C.c_int32 * 2)(10, 10)
+    for size in (L.tgl_mfg_workspace, lambda n: L.tgl_tcsr_build_workspace(n, 1000, 1),
+                 lambda n: L.tgl_sample_workspace(n, 2, fan, 1), lambda n: L.tgl_sample_workspace(n, 2, fan, 3)):
+        got = [int(size(n)) for n in edges]
+        assert all(a <= b for a, b in zip(got, got[1:]))
