@@ -9,10 +9,17 @@
 
 namespace tgl {
 
+// Four floats loaded at once from an address that is a multiple of 4 bytes: the
+// timestamps tgl_tcsr_nodes is given need no other alignment.
+using f32x4 = float __attribute__((ext_vector_type(4), aligned(4)));
+
 // ts[p4 .. p4+3] for p4 a multiple of 4; entries at or past M read as +inf
 // (they are never inside a window).
 __device__ __forceinline__ float4 load_ts4(const float *__restrict__ tsa, uint32_t p4, uint32_t M) {
-    if (static_cast<uint64_t>(p4) + 3 < M) return *reinterpret_cast<const float4 *>(tsa + p4);
+    if (static_cast<uint64_t>(p4) + 3 < M) {
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(tsa + p4);
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
     const float inf = __builtin_inff();
     float4 r = make_float4(inf, inf, inf, inf);
     if (p4 < M) r.x = tsa[p4];

@@ -52,3 +52,24 @@ def test_run_lengths(kind, index, tdir):
             assert np.array_equal(got[:, 0], lo) and np.array_equal(got[:, 1], hi)
             assert np.array_equal(g.first_hint.cpu().numpy(), first_hints(og.indptr, og.nbr, og.ts))
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("index,tdir", [(True, True), (True, False), (False, False)])
+def test_unaligned_times(index, tdir):
+    """tgl_tcsr_nodes takes timestamps at any multiple of 4 bytes: the same
+    histories, directories and index from slices at 0, 4, 8 and 12 bytes."""
+    torch = require_gpu()
+    rng = np.random.default_rng(4)
+    m, n = 60_000, 300
+    src, dst = (rng.integers(0, n, m).astype(np.int32) for _ in range(2))
+    g = P.tcsr_build(upload(src), upload(dst), upload(rng.random(m).astype(np.float32)), None, n, True)
+    nbr, eid = P.tcsr_columns(g)
+    buf = torch.empty(g.num_entries + 4, device="cuda")
+    for off in range(4):
+        announce("index=%s dir=%s offset %d" % (index, tdir, off))
+        ts = buf[off:off + g.num_entries]
+        ts.copy_(g.ts)
+        c = P.tcsr_from_columns(g.indptr, nbr, ts, eid, index=index, dir=tdir)
+        assert torch.equal(c.hist, g.hist) and torch.equal(c.entries, g.entries) and torch.equal(c.nodes, g.nodes)
+        assert not tdir or torch.equal(c.dir, g.dir)
+        assert not index or torch.equal(c.ts_index, g.ts_index)
