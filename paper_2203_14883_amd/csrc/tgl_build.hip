@@ -644,20 +644,23 @@ __global__ __launch_bounds__(kBlock) void fill_first_kernel(F *__restrict__ a, i
         a[i] = first_none<F>();
 }
 
-// Edge k as one 16-byte record {src, dst, eid}.  When the sort key does not
+// Edge k as one 16-byte record {src, dst, eid}, in workspace that may be aligned to
+// 8 bytes only.  When the sort key does not
 // hold the neighbour and the caller gave edge ids, writing an entry gathers
 // both by edge index, which for a shuffled list is a random line each: 10.1
 // ms for the 200M entries of a shuffled 100M-edge list, against 5.8 ms from
 // records plus 0.6 ms to write them.
+using EdgeRecord = int __attribute__((ext_vector_type(4), aligned(8)));
+
 __global__ __launch_bounds__(kBlock) void pack_edges_kernel(const int32_t *__restrict__ src,
                                                             const int32_t *__restrict__ dst,
                                                             const int64_t *__restrict__ eid, int64_t m0,
-                                                            int4 *__restrict__ edges) {
+                                                            EdgeRecord *__restrict__ edges) {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < m0; k += stride) {
         const int64_t e = eid[k];
-        edges[k] = make_int4(src[k], dst[k], static_cast<int>(static_cast<uint32_t>(e)),
-                             static_cast<int>(static_cast<uint64_t>(e) >> 32));
+        edges[k] = EdgeRecord{src[k], dst[k], static_cast<int>(static_cast<uint32_t>(e)),
+                              static_cast<int>(static_cast<uint64_t>(e) >> 32)};
     }
 }
 
@@ -675,7 +678,7 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(const uint64_t *__restrict
                                                       int64_t m0, const int32_t *__restrict__ src,
                                                       const int32_t *__restrict__ dst,
                                                       const int64_t *__restrict__ eid,
-                                                      const int4 *__restrict__ edges, int64_t N,
+                                                      const EdgeRecord *__restrict__ edges, int64_t N,
                                                       const KeyLayout L, const F *__restrict__ first,
                                                       int64_t *__restrict__ indptr,
                                                       int4 *__restrict__ ent,
@@ -699,7 +702,7 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(const uint64_t *__restrict
         int32_t v[kEmitPerLane];
         int64_t e[kEmitPerLane];
         if (edges) {                               // uniform
-            int4 r[kEmitPerLane];
+            EdgeRecord r[kEmitPerLane];
 #pragma unroll
             for (int j = 0; j < kEmitPerLane; j++) r[j] = edges[k[j]];
 #pragma unroll
@@ -844,7 +847,7 @@ __device__ __forceinline__ int sum8(int v) {
 // With neither (kByHalves) a lane searches the run of its own entry by halves:
 // 8 lanes that probe it in 8 places a round fetch eight lines where a half
 // takes one, and take 8.8 ms for the histories of 40M entries of three million
-// nodes where this takes 4.5 (2.9 with the index, 2.4 with directories).
+// nodes where this takes 4.3 (3.1 with the index, 2.4 with directories).
 // One lane per entry, reading its record in eight 16-byte loads and searching
 // the run by halves, fetched a record's line up to eight times over (64
 // lanes' lines do not stay in a 32 KB L1) and took a dependent load per
@@ -1287,9 +1290,9 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
     const int fbytes = L.packed && L.ts_bits <= 8 ? 1 : (L.packed && L.ts_bits <= 16 ? 2 : 4);
     void *const first = !hist_out && num_nodes * fbytes <= 8 * M ? static_cast<void *>(w.keys[cur ^ 1]) : nullptr;
     // the spare key buffer (8 bytes per entry) holds a record per edge of an undirected list
-    int4 *edges = nullptr;
+    EdgeRecord *edges = nullptr;
     if (hist_out && eid && !L.packed && M == 2 * m0) {
-        edges = reinterpret_cast<int4 *>(w.keys[cur ^ 1]);
+        edges = reinterpret_cast<EdgeRecord *>(w.keys[cur ^ 1]);
         pack_edges_kernel<<<grid_for(m0), kBlock, 0, st>>>(src, dst, eid, m0, edges);
     }
     const unsigned gm = grid_for(M), gn = grid_for(num_nodes);

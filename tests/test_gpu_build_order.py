@@ -74,3 +74,21 @@ def test_histogram_sizes(m):
     want = oracle.build_tcsr(src, dst, ts, None, 9000, True)
     assert np.array_equal(got.indptr, want.indptr) and np.array_equal(got.eid, want.eid)
     assert np.array_equal(got.nbr, want.nbr) and np.array_equal(got.ts, want.ts)
+
+
+def test_unaligned_workspace():
+    """A workspace at any multiple of 8 bytes, with the records of an edge per
+    entry (a key without the neighbour, edge ids given)."""
+    torch = require_gpu()
+    rng = np.random.default_rng(8)
+    m, nodes = 30_000, 1 << 22
+    src, dst = (upload(rng.integers(0, nodes, m).astype(np.int32)) for _ in range(2))
+    ts = upload(rng.standard_normal(m).astype(np.float32) * 1e6)
+    eid = upload(rng.integers(-5, 1 << 40, m))
+    need = P.binding.tcsr_build_workspace(m, nodes, True)
+    want = P.tcsr_build(src, dst, ts, eid, nodes, True)
+    for off in (8, 24, 40):
+        announce("workspace offset %d" % off)
+        ws = torch.empty(need + off, dtype=torch.uint8, device="cuda")[off:]
+        got = P.tcsr_build(src, dst, ts, eid, nodes, True, workspace=ws)
+        assert torch.equal(got.entries, want.entries) and torch.equal(got.indptr, want.indptr)
