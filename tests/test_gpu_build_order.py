@@ -92,3 +92,28 @@ def test_unaligned_workspace():
         ws = torch.empty(need + off, dtype=torch.uint8, device="cuda")[off:]
         got = P.tcsr_build(src, dst, ts, eid, nodes, True, workspace=ws)
         assert torch.equal(got.entries, want.entries) and torch.equal(got.indptr, want.indptr)
+
+
+@pytest.mark.parametrize("m", [17_000_001, 34_000_003])
+def test_blocks_of_several_tiles(m):
+    """Lists in time order of so many edges that a block of the merge takes
+    two or three tiles of 2048 in a row and carries the time that leaves one to
+    the next: all times equal, a few long ties whose ends lie off the tiles'
+    (most spanning whole tiles), ties of about a tile, and short ones.  Every
+    field against two stable sorts on the device."""
+    torch = require_gpu()
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    nodes = 1_000_000
+    src, dst = (torch.randint(0, nodes, (m,), generator=gen, device="cuda", dtype=torch.int32) for _ in range(2))
+    for ties in (1, 9, 3000, m // 2048, m // 3):
+        announce("edges %d times %d" % (m, ties))
+        ts = torch.randint(0, ties, (m,), generator=gen, device="cuda").sort().values.float()
+        g = P.tcsr_build(src, dst, ts, None, nodes, True, hist=False)
+        own = torch.cat([src, dst])
+        order = torch.cat([ts, ts]).sort(stable=True).indices
+        order = order[own[order].sort(stable=True).indices]
+        assert torch.equal(g.nbr, torch.cat([dst, src])[order])
+        assert torch.equal(g.eid, order % m)
+        assert torch.equal(g.ts, torch.cat([ts, ts])[order])
+        assert torch.equal(g.indptr[1:], torch.bincount(own, minlength=nodes).cumsum(0)) and int(g.indptr[0]) == 0
+        del g, order, own
