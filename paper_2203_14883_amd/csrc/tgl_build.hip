@@ -58,10 +58,14 @@ unsigned radix_grid(int64_t ntiles) {
 
 struct BuildFlags {
     uint32_t err;
-    uint32_t unsorted;          // some edge is older than the one before it
-    uint64_t or_bits;
+    uint64_t or_bits;           // and kUnsorted: some edge is older than the one before it
     uint64_t and_bits;
 };
+
+// Bit 63 of or_bits: the node ids of a valid list are below 2^31.  A flag of its
+// own is one more atomic per block on the same line, for a list in no order
+// 11 us of 300 at a million edges.
+constexpr uint64_t kUnsorted = 1ull << 63;
 
 __device__ __forceinline__ uint32_t ts_key(float t) {
     const uint32_t b = __float_as_uint(t == 0.0f ? 0.0f : t);   // -0 -> +0
@@ -89,7 +93,6 @@ __device__ __forceinline__ T wave_and(T v) {
 
 __global__ void init_flags_kernel(BuildFlags *f) {
     f->err = 0;
-    f->unsorted = 0;
     f->or_bits = 0;
     f->and_bits = ~0ull;
 }
@@ -199,10 +202,10 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const int32_t *__restric
         }
 #pragma unroll
         for (int i = 0; i < kWaves; i++) bb |= s_bad[i];
+        if (bb & 2u) o |= kUnsorted;
         atomicOr(reinterpret_cast<unsigned long long *>(&flags->or_bits), static_cast<unsigned long long>(o));
         atomicAnd(reinterpret_cast<unsigned long long *>(&flags->and_bits), static_cast<unsigned long long>(a));
         if (bb & 1u) atomicOr(&flags->err, 1u);
-        if (bb & 2u) atomicOr(&flags->unsorted, 1u);
     }
 }
 
@@ -1147,8 +1150,8 @@ KeyLayout key_layout(const BuildFlags &f, int64_t N) {
 // Key bits the sort must order by: the varying node and tskey bits where the
 // layout puts them (never the neighbour bits, so ties keep input order).
 // With the keys already in time order only the node bits are left.
-uint64_t sort_bits(const KeyLayout &L, const BuildFlags &f) {
-    const uint64_t var = (f.or_bits ^ f.and_bits) & (f.unsorted ? ~0ull : 0xFFFFFFFF00000000ull);
+uint64_t sort_bits(const KeyLayout &L, const BuildFlags &f, bool unsorted) {
+    const uint64_t var = (f.or_bits ^ f.and_bits) & (unsorted ? ~0ull : 0xFFFFFFFF00000000ull);
     if (!L.packed) return var;
     const uint64_t nv = ((var >> 32) >> L.node_lo) & low_mask(L.node_bits);
     const uint64_t tv = ((var & 0xFFFFFFFFull) >> L.ts_lo) & low_mask(L.ts_bits);
@@ -1226,10 +1229,12 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
         return TGL_EDEVICE;
     if (hipStreamSynchronize(st) != hipSuccess) return TGL_EDEVICE;
     if (hf.err) return TGL_ERANGE;
+    const bool unsorted = (hf.or_bits & kUnsorted) != 0;
+    hf.or_bits &= ~kUnsorted;
 
     const KeyLayout L = key_layout(hf, num_nodes);
-    const uint64_t varying = sort_bits(L, hf);
-    if (!hf.unsorted && M != m0) {
+    const uint64_t varying = sort_bits(L, hf, unsorted);
+    if (!unsorted && M != m0) {
         const int64_t tiles = (m0 + kMergeTile - 1) / kMergeTile, per = (tiles + kMergeBlocks - 1) / kMergeBlocks;
         merged_keys_kernel<<<static_cast<unsigned>((tiles + per - 1) / per), kBlock, 0, st>>>(src, dst, ts, m0, per, L,
                                                                                               w.keys[0], w.vals[0]);
