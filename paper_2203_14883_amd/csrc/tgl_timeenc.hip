@@ -264,18 +264,18 @@ __host__ __device__ __forceinline__ uint32_t word_blocks(int64_t words, int lane
 // stores the kAhead before them.  Loads and stores complete in order, so that a
 // load after a store waits for it too, and with a load per word that is what a
 // word took where dt came from memory (a step's 8M slots, half of them PAD, 100
-// float32: 856 -> 593 us; dt in the cache 566 -> 592).
+// float32: 856 -> 597 us; dt in the cache and no PAD 566 -> 580).
 //
 // The argument is one double fma per element, in quarter turns; one float fma
 // per word tells whether any of its arguments needs far_quarters.  What an
 // element becomes depends on its own dt, omega and phi alone.  19 instructions
 // per float32 element, 5 of them double.  Against the reduction to turns, fold
 // and Taylor series of timeenc_kernel with the factors in LDS (same inputs,
-// before -> now): 100 float32 of 8M slots 691 -> 593 us with dt in memory (5.7
-// TB/s; a plain fill writes 6.9) and 827 -> 605 with dt in the cache and no PAD,
-// 101 of 2M 396 -> 204, 100 bfloat16 of 8M 1025 -> 470 and 1156 -> 520; where a
+// before -> now): 100 float32 of 8M slots 692 -> 597 us with dt in memory (5.7
+// TB/s; a plain fill writes 6.9) and 824 -> 580 with dt in the cache and no PAD,
+// 101 of 2M 395 -> 197, 100 bfloat16 of 8M 1027 -> 454 and 1157 -> 505; where a
 // third of the slots have arguments of 2^24 turns or more, 100 float32 of 2M
-// 395 -> 186, 172 bfloat16 498 -> 285.
+// 396 -> 181, 172 bfloat16 499 -> 275.
 template <int OUT, bool STRADDLE>
 __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__restrict__ dt, int64_t n,
                                                               const int64_t *__restrict__ count, int64_t per,
@@ -311,35 +311,39 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
         om = fmaxf(om, fabsf(omega[j]));
         pm = fmaxf(pm, fabsf(phi[j]));
     }
+    // the lane's words: every lane of the launch has total / T, some one more
+    const int64_t each = total / T;
+    int64_t left = each + (w < total - each * T);
+    i32x4 *o = static_cast<i32x4 *>(out) + w;
+    const i32x4 *const o_last = static_cast<i32x4 *>(out) + (total - 1);
     // time differences of the lane's next kAhead words (STRADDLE: and of the rows
-    // after theirs); past its last word, of a row that is there
+    // after theirs); past its last word, of its first row
     struct Ahead {
         float d0[kAhead], d1[kAhead];
     };
-    const auto load_ahead = [&](int64_t w0, int64_t r0) {
+    const int64_t row0 = row;
+    const auto load_ahead = [&](int64_t r0, int64_t words) {
         Ahead a;
 #pragma unroll
         for (int u = 0; u < kAhead; u++) {
-            const int64_t r = w0 + u * T < total ? r0 + u * row_step : row;
+            const int64_t r = u < words ? r0 + u * row_step : row0;
             a.d0[u] = dt[r];
             a.d1[u] = STRADDLE ? dt[r + 1 < n ? r + 1 : r] : a.d0[u];
         }
         return a;
     };
-    Ahead now = load_ahead(w, row);
+    Ahead now = load_ahead(row, left);
     // in registers here, so that the loop holds no wait for them
 #pragma unroll
     for (int u = 0; u < kAhead; u++) asm volatile("" : "+v"(now.d0[u]), "+v"(now.d1[u]));
     for (;;) {
-        const Ahead next = load_ahead(w + kAhead * T, row + kAhead * row_step);
-#pragma unroll 1
-        for (int u = 0; u < kAhead && w < total; u++, w += T, row += row_step) {
-            const float d0 = now.d0[0], d1 = now.d1[0];
-#pragma unroll
-            for (int i = 0; i + 1 < kAhead; i++) {
-                now.d0[i] = now.d0[i + 1];
-                now.d1[i] = now.d1[i + 1];
-            }
+        row += kAhead * row_step;
+        const Ahead next = load_ahead(row, left - kAhead);
+        const int words = left < kAhead ? static_cast<int>(left) : kAhead;
+#pragma unroll                                                      // 4% over a loop that moves now.d0 down
+        for (int u = 0; u < kAhead; u++, o += T) {
+            if (u >= words) break;
+            const float d0 = now.d0[u], d1 = now.d1[u];
             float v[EPW];
 #pragma unroll
             for (int e = 0; e < EPW; e++) v[e] = 0.0f;
@@ -384,12 +388,12 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
                         if (col + e >= dim ? pad1 : pad0) v[e] = 0.0f;
                 }
             }
-            if (STRADDLE && w * EPW + EPW > elems) {                    // the last word, cut short
+            if (STRADDLE && o == o_last && elems % EPW != 0) {          // the last word, cut short
 #pragma unroll
                 for (int e = 0; e < EPW; e++) {
-                    if (w * EPW + e >= elems) continue;
-                    if constexpr (OUT == TGL_OUT_F32) static_cast<float *>(out)[w * EPW + e] = v[e];
-                    else static_cast<uint16_t *>(out)[w * EPW + e] = to_bf16(v[e]);
+                    if (e >= static_cast<int>(elems % EPW)) continue;
+                    if constexpr (OUT == TGL_OUT_F32) reinterpret_cast<float *>(o)[e] = v[e];
+                    else reinterpret_cast<uint16_t *>(o)[e] = to_bf16(v[e]);
                 }
             } else {
                 i32x4 word;
@@ -398,10 +402,11 @@ __global__ __launch_bounds__(kBlock) void timeenc_word_kernel(const float *__res
                 } else {
                     word = i32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
                 }
-                __builtin_nontemporal_store(word, static_cast<i32x4 *>(out) + w);
+                __builtin_nontemporal_store(word, o);
             }
         }
-        if (w >= total) break;
+        left -= kAhead;
+        if (left <= 0) break;
         now = next;
     }
 }
@@ -436,16 +441,16 @@ unsigned resident_grid(K kernel, int variant, int64_t want) {
 
 int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
 
-// Words per lane, which make its setup (a division, its columns' factors)
-// small: 100 float32 of 600,000 slots take 60 us with 4 and 51 with 8; of 18,000
-// slots 6 with 8 and 9 with 16.  And blocks at most, so that a call for many slots
+// Words per lane, which make its setup (two divisions, its columns' factors)
+// small: 100 float32 of 600,000 slots take 60 us with 4 and 50 with 8; of 18,000
+// slots 6 with 8 and 8 with 16.  And blocks at most, so that a call for many slots
 // of which the device counts few does not wait for empty blocks (20M slots, 2,000
 // of them valid: 6, 9 and 16 us on 4096, 8192 and 16384 blocks, 100 on as many as
 // there are words for).  Full calls on 4096 / 8192 / 16384 / 25600 blocks: 100
-// float32 of 8M slots 636 / 603 / 605 / 614 us, 172 of 2M 260 / 261 / 269 / 279,
-// 128 of 2M 264 / 240 / 203 / 214; bfloat16 on 4096 / 6144 / 8192 / 25600: 100 of
-// 8M 516 / 519 / 523 / 556, 128 of 2M 135 / 140 / 148 / 253, 100 of 64M 4219 / 4139
-// / 4116 / 4089.
+// float32 of 8M slots 662 / 599 / 580 / 592 us, 172 of 2M 271 / 252 / 260 / 273,
+// 128 of 2M 269 / 237 / 198 / 209; bfloat16 on 4096 / 6144 / 8192 / 25600: 100 of
+// 8M 499 / 500 / 507 / 551, 128 of 2M 134 / 140 / 147 / 259, 100 of 64M 3998 / 3964
+// / 3943 / 3931.
 constexpr int kLaneWordsF32 = 8;
 constexpr int kLaneWordsBf16 = 4;
 constexpr uint32_t kMostF32 = 16384;
