@@ -8,11 +8,13 @@
 // tskeys, so bits on which every entry agrees are known before any key is
 // written.  It also sees whether the edges come in time order, as recorded
 // interactions do: the keys are then written in the order of (time, entry
-// index), and the sort runs over the node bits alone (c4: four passes instead
-// of five; a Wikipedia-sized list: two instead of six).  When the varying node bits, the varying tskey bits and the
-// neighbour id fit in 64 bits together (c4: 27 + 8 + 27), a key packs them in
-// that order: the sort runs over the node and tskey fields only (five 8-bit
-// passes for c4 instead of six), and the neighbour id rides in the low bits,
+// index), and the sort runs over the node bits alone (1.3 billion edges of 121.7
+// million nodes with 121 times: four passes instead of five; a Wikipedia-sized
+// list: two instead of six).  When the varying node bits, the varying tskey bits
+// and the neighbour id fit in 64 bits together (27 + 8 + 27 for those edges), a
+// key packs them in that order: the sort runs over the node and tskey fields
+// only (five passes for such edges in no order, instead of six), and the
+// neighbour id rides in the low bits,
 // so writing the entries reads the sorted keys and indices in order instead
 // of gathering each neighbour by original edge index.  Otherwise the key is
 // (node << 32 | tskey) and the digits every key shares are skipped.  Each
@@ -1245,7 +1247,7 @@ tgl_status tgl_tcsr_build(const int32_t *src, const int32_t *dst, const float *t
     // neighbour bits lie below every sort bit: they must not take part, or
     // ties would leave input order).  The span from there to the highest
     // varying bit is cut into as few passes as 8-bit digits allow, `step`
-    // bits apart (c4: 35 bits, five 7-bit digits).  A pass reads a digit of
+    // bits apart (27 bits: four 7-bit digits, 35: five).  A pass reads a digit of
     // kb = 7 or 8 bits at its shift; when step is below 7 the digits overlap,
     // which leaves the LSD order unchanged.  A digit on which every key agrees
     // is skipped.

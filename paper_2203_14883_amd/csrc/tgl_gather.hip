@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const GatherArgs a) {
         int64_t src[kFlat];
 #pragma unroll
         for (int u = 0; u < kFlat; u++) {
-            // r < W + kSpan <= 4608, so r / W is exactly r * recip >> 32
+            // r < W + kSpan <= 4352, so r / W is exactly r * recip >> 32
             const uint32_t r = off0 + static_cast<uint32_t>(u * kWave + lane);
             const uint32_t q = W == 1 ? r : __umulhi(r, T.recip);
             const int64_t row = row0 + q < n ? row0 + q : n - 1;    // clamped: loads issue together

@@ -37,7 +37,7 @@ constexpr int64_t kSmallGroups = int64_t(1) << 20;
 int tile_groups(int64_t groups_cap) { return groups_cap <= kSmallGroups ? kTileLeast : kTileMost; }
 
 // A group as the scatter reads it: its first edge within the tile (below
-// kTileMost * TGL_MAX_FANOUT = 2^21) and its valid slots (at most 2^10).
+// kTileMost * TGL_MAX_FANOUT = 2^20) and its valid slots (at most 2^10).
 constexpr int kCountBits = 11;
 static_assert(TGL_MAX_FANOUT < (1 << kCountBits) &&
                   int64_t(kTileMost) * TGL_MAX_FANOUT <= int64_t(1) << (32 - kCountBits),
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void mfg_count_kernel(const int32_t *__rest
     for (int i = 0; i < GPT; i++) s_cnt[i * kBlock + threadIdx.x] = k;
     __syncthreads();
     const int32_t *const sl = nbr + tile0 * k;
-    const int n = ng * k;                           // at most 2^21
+    const int n = ng * k;                           // at most 2^20
     for (int i0 = 0; i0 < n; i0 += kCountUnroll * kBlock) {
         int32_t v[kCountUnroll], before[kCountUnroll];
 #pragma unroll

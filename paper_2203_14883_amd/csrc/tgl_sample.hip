@@ -23,7 +23,7 @@
 //   4. next hop: valid slots are a prefix of every (root, window) group, so an
 //      exclusive scan of the per-group counts gives every next-hop root its
 //      index.  The next hop's kernel walks the previous hop's slots directly
-//      ("virtual roots"): each wavefront loads 64 of them, compacts the valid
+//      ("virtual roots"): each wavefront loads up to 64 of them, compacts the valid
 //      ones through LDS, and serves them G lanes per root.  No list of next-hop
 //      roots is materialised.
 //
@@ -85,7 +85,8 @@ struct HopArgs {
     int32_t hop;                // 1-based
     int32_t k;
     int32_t windows;            // windows per root: S on hop 1, 1 afterwards
-    int32_t chunk;              // candidate roots per wavefront and round: 64, or fewer for small calls
+    int32_t chunk;              // candidate roots per wavefront and round (pick_chunk): 32 or fewer
+                                // on hop 1, 64 or fewer later
     float delta;
     int32_t delta_inf;
     int32_t anchor;             // TGL_ANCHOR_OWN / TGL_ANCHOR_ROOT (windows of hops >= 2)
@@ -469,7 +470,7 @@ __device__ __forceinline__ void multi_root(const HopArgs &p, int64_t q, int32_t 
 }
 
 // First hop with more than kMultiEdges - 1 windows.  Each wavefront takes
-// chunks of 64 roots:
+// chunks of up to 32 roots (pick_chunk):
 //   phase 1, one lane per root: its time, path key and node summary are
 //     packed into LDS;
 //   phase 2, G lanes per root, 64 / G roots per round: the S + 1 window
@@ -534,7 +535,7 @@ __global__ __launch_bounds__(kBlock) void hop_multi_wide_kernel(const HopArgs p)
 }
 
 // First hop with S > 1 windows, S + 1 <= kMultiEdges.  Each wavefront takes
-// chunks of 64 roots:
+// chunks of up to 32 roots (pick_chunk):
 //   phase 1, one lane per root: its time, path key and node summary are
 //     packed into LDS;
 //   phase 2, 8 lanes per root, 8 roots per round: the S + 1 window edges,
@@ -768,7 +769,7 @@ __device__ __forceinline__ void locate_window(const HopArgs &p, int32_t x, uint3
 }
 
 // One hop with one window per root (every hop except a first hop with several
-// snapshots).  Each wavefront takes chunks of 64 candidate roots:
+// snapshots).  Each wavefront takes chunks of up to 64 candidate roots, 32 on hop 1:
 //   phase 1, one lane per candidate: hop 1 takes root v as given; later hops
 //     take slot v of the previous hop, valid when its nbr >= 0, as the root
 //     with index off(g) + j for g = v / k_prev, j = v % k_prev, off the
